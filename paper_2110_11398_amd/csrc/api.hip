@@ -51,11 +51,11 @@ struct abacus_nf_cells_s {
     int64_t wcap_cells = -1, wcap_items = -1, wcap_partials = -1, wcap_boxes = -1;
     ForceBox *d_fbox = nullptr;
     WorkState *ws = nullptr;
+    WorkBox *wb = nullptr;
     Item *items = nullptr;
     int32_t *cell_nsrc = nullptr, *cell_parts = nullptr;
-    int64_t *cell_pdem = nullptr, *cell_pbase = nullptr;
+    int64_t *cell_pbase = nullptr;
     double *partials = nullptr;
-    void *wscan_temp = nullptr;
     // largest |a|^2 per cell (bits of a non-negative double) written by the last forces call; valid until
     // the next build
     unsigned long long *cell_amax = nullptr;
@@ -147,11 +147,9 @@ void free_step_buffers(abacus_nf_cells_s *h) {
 }
 
 void free_work_buffers(abacus_nf_cells_s *h) {
-    dfree(h->d_fbox); dfree(h->ws); dfree(h->items); dfree(h->cell_nsrc); dfree(h->cell_parts);
-    dfree(h->cell_pdem); dfree(h->cell_pbase); dfree(h->partials); dfree(h->cell_amax);
+    dfree(h->d_fbox); dfree(h->ws); dfree(h->wb); dfree(h->items); dfree(h->cell_nsrc); dfree(h->cell_parts);
+    dfree(h->cell_pbase); dfree(h->partials); dfree(h->cell_amax);
     h->amax_valid = false;
-    if (h->wscan_temp) hipFree(h->wscan_temp);
-    h->wscan_temp = nullptr;
     h->wcap_cells = h->wcap_items = h->wcap_partials = h->wcap_boxes = -1;
 }
 
@@ -164,7 +162,9 @@ int key_bits(int64_t n_cells) {
 abacus_nf_tuning default_tuning() {
     abacus_nf_tuning t;
     memset(&t, 0, sizeof(t));
-    t.sinks_per_lane = 2;
+    // four sinks per lane and two sources a step: eight reciprocal square roots issued together (clustered box of
+    // 256^3 particles: 99.9 ms; two sinks and two or four sources 104, four sinks and one source 104)
+    t.sinks_per_lane = 4;
     t.chunk = 256;
     t.unroll = 2;
     t.max_lanes = 64;
@@ -356,15 +356,18 @@ static int ensure_work_buffers(abacus_nf_cells_s *h) {
     const int64_t want_items = h->tune.item_capacity > 0
                                    ? h->tune.item_capacity
                                    : std::min<int64_t>(INT32_MAX - 1, std::min(n, nc) + n / 16 + n / 11 + (1 << 16));
-    const int64_t want_partials = 2 * n + (1 << 16);
+    // split lists: a partial slot per sink and part; every box has room for the parts that fill the chip with it
+    // alone (64 lanes x 4 sinks x kFillItems items at most; parts of kMinPart iterations in small boxes)
+    int64_t want_partials = 2 * n + (1 << 16);
+    for (const abacus_nf_box &b : h->boxes)
+        want_partials += std::min<int64_t>(32 * b.n, (int64_t)(256 * kFillItems));
     if (h->wcap_cells >= nc && h->wcap_items == want_items && h->wcap_partials >= want_partials &&
         h->wcap_boxes >= h->n_boxes)
         return ABACUS_NF_OK;
     free_work_buffers(h);
-    bool ok = dalloc(h->d_fbox, h->n_boxes) && dalloc(h->ws, 1) && dalloc(h->items, want_items) &&
-              dalloc(h->cell_nsrc, nc) && dalloc(h->cell_parts, nc) && dalloc(h->cell_pdem, nc) &&
-              dalloc(h->cell_pbase, nc) && dalloc(h->partials, 4 * want_partials) && dalloc(h->cell_amax, nc) &&
-              dalloc_bytes(h->wscan_temp, scan_temp_bytes(nc));
+    bool ok = dalloc(h->d_fbox, h->n_boxes) && dalloc(h->ws, 1) && dalloc(h->wb, h->n_boxes) &&
+              dalloc(h->items, want_items) && dalloc(h->cell_nsrc, nc) && dalloc(h->cell_parts, nc) &&
+              dalloc(h->cell_pbase, nc) && dalloc(h->partials, 4 * want_partials) && dalloc(h->cell_amax, nc);
     if (!ok) {
         free_work_buffers(h);
         return ABACUS_NF_ENOMEM;
@@ -394,7 +397,7 @@ static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf
     a.ws = h->ws;
     a.cell_nsrc = h->cell_nsrc;
     a.cell_parts = h->cell_parts;
-    a.cell_pdem = h->cell_pdem;
+    a.wb = h->wb;
     a.cell_pbase = h->cell_pbase;
     a.partials = h->partials;
     a.partial_capacity = h->wcap_partials;
@@ -405,7 +408,6 @@ static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf
     a.kind = kind;
     a.mode = mode;
     a.tune = h->tune;
-    a.scan_temp = h->wscan_temp;
     return a;
 }
 
@@ -746,12 +748,14 @@ int abacus_nf_interactions(abacus_nf_cells h, void *hip_stream, int64_t *out) {
     if (rc != ABACUS_NF_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     ForcesArgs a = make_args(h, ABACUS_NF_SPLINE, ABACUS_NF_SUM_FP32, nullptr, device_error_word(dev));
-    hipError_t e = launch_count_interactions(a, st);
+    hipError_t e = launch_count_interactions(a, false, st);
     if (e != hipSuccess) return hip_fail(e);
-    unsigned long long v = 0;
-    if (hipMemcpyAsync(&v, &h->ws->interactions, sizeof(v), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    std::vector<WorkBox> wb((size_t)h->n_boxes);
+    if (hipMemcpyAsync(wb.data(), h->wb, wb.size() * sizeof(WorkBox), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return hip_fail(hipErrorUnknown);
+    unsigned long long v = 0;
+    for (const WorkBox &b : wb) v += b.pairs;
     *out = (int64_t)v;
     return ABACUS_NF_OK;
 }

@@ -384,10 +384,6 @@ hipError_t scan_i32_max_inclusive(const int32_t *in, int32_t *out, int64_t n, vo
     return scan_impl<int32_t, OpMax>(in, out, n, true, (int32_t)0, (char *)temp, st);
 }
 
-hipError_t scan_i64_add_exclusive(const int64_t *in, int64_t *out, int64_t n, void *temp, hipStream_t st) {
-    return scan_impl<int64_t, OpAdd>(in, out, n, false, (int64_t)0, (char *)temp, st);
-}
-
 size_t radix_temp_bytes(int64_t n) {
     int64_t ntiles = (n + kTile - 1) / kTile;
     int64_t hist = ntiles * kRadixBins;

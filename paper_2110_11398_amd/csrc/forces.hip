@@ -7,11 +7,10 @@
 // Sec. 4.5).  Here the work list is built on the device and one persistent
 // launch drains it:
 //
-//   k_wl_cells    per cell: occupancy n_c, near-field source count, pair total
-//   k_wl_plan     scales the source-part length so partial slots fit
-//   k_wl_count    per cell: tiles x parts, cost class (histogram over classes)
-//   k_wl_classes  class offsets (heaviest items first), capacity checks
-//   k_wl_emit     items written in class order
+//   k_wl_cells    per cell: occupancy n_c, near-field source count; per box: pair and work totals
+//   k_wl_plan     the source-part length of every box
+//   k_wl_count    per cell: tiles x parts, partial slots, cost class (histogram over classes)
+//   k_wl_emit     class offsets (heaviest items first), capacity checks, items in class order
 //   k_forces      persistent waves pop items: sink tile in VGPRs, sources staged
 //                 through the wave's LDS region with the periodic cell offset
 //                 applied, FP32 pair math, FP32 / two-sum / FP64 accumulation,
@@ -109,53 +108,47 @@ __device__ inline int cell_sources(const int32_t *__restrict__ cs, const BoxDev 
     return total;
 }
 
-// Tiles, parts and cost class of one cell.
-struct CellPlan {
-    int tiles, parts, cls;
-    int64_t items;
-};
-
-__device__ inline CellPlan plan_cell(int n, int nsrc, int S, int max_lanes, int part_iters) {
-    CellPlan p;
-    if (n <= 0) {
-        p.tiles = p.parts = 0;
-        p.items = 0;
-        p.cls = kNumClasses - 1;
-        return p;
-    }
-    p.tiles = tile_count(n, S, max_lanes);
-    const int L0 = tile_at(n, S, max_lanes, 0).L;               // the heaviest tile: fewest lanes per group
-    const int64_t iters = ((int64_t)nsrc + L0 - 1) / L0;        // source iterations per lane
+// Parts of the source list of a cell: as many as keep its first tile (fewest lanes per group) at about
+// part_iters source iterations per lane.
+__device__ inline int cell_part_count(int n, int nsrc, int S, int max_lanes, int part_iters) {
+    if (n <= 0) return 0;
+    const int L0 = tile_at(n, S, max_lanes, 0).L;
+    const int64_t iters = ((int64_t)nsrc + L0 - 1) / L0;
     int64_t parts = (iters + part_iters - 1) / part_iters;
     if (parts < 1) parts = 1;
     if (parts > nsrc) parts = nsrc > 0 ? nsrc : 1;
-    p.parts = (int)parts;
-    p.items = (int64_t)p.tiles * p.parts;
-    // cost of one item ~ iterations per lane x sinks per lane; classes are half octaves, heaviest first
-    const double cost = (double)(iters / parts + 1) * S + 16.0;
-    int cls = kNumClasses - 1 - (int)(2.0 * log2(cost));
-    p.cls = cls < 0 ? 0 : (cls >= kNumClasses ? kNumClasses - 1 : cls);
-    return p;
+    return (int)parts;
+}
+
+// Cost class of a cell's items: one part of its source list against its first tile, iterations per lane x sinks
+// per lane; classes are half octaves, heaviest first.  The tiles of a cell's rest are lighter and share the
+// class on purpose: they wait on their loads more than they compute, and run best among heavier items (with a
+// class of their own, at the end of the list: uniform box of 2097152 particles 4.77 -> 5.07 ms).
+__device__ inline int cell_class(int n, int nsrc, int S, int max_lanes, int parts) {
+    const int L0 = tile_at(n, S, max_lanes, 0).L;
+    const int iters = (nsrc + L0 - 1) / L0;
+    const float cost = (float)(iters / parts + 1) * (float)S + 16.0f;
+    const int cls = kNumClasses - 1 - (int)(2.0f * log2f(cost));
+    return cls < 0 ? 0 : (cls >= kNumClasses ? kNumClasses - 1 : cls);
 }
 
 // ---------------------------------------------------------------- work-list kernels
 
-__global__ void k_wl_clear(WorkState *ws, int part_iters) {
-    int t = threadIdx.x;
-    if (t == 0) {
-        ws->interactions = 0;
-        ws->part_demand = 0;
-        ws->base_items = 0;
-        ws->split_items = 0;
-        ws->n_items = 0;
-        for (int q = 0; q < kQueues; q++) ws->cursor[q] = 0;
-        ws->part_iters = part_iters;
-        ws->overflow = 0;
-    }
-    if (t < kNumClasses) {
-        ws->class_count[t] = 0;
-        ws->class_fill[t] = 0;
-        ws->class_base[t] = 0;
+__global__ __launch_bounds__(256) void k_wl_clear(WorkState *ws, WorkBox *wb, int n_boxes) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n_boxes) wb[i] = WorkBox{0, 0, 0, 0, 0, 0};
+    if (blockIdx.x == 0) {
+        const int t = threadIdx.x;
+        if (t == 0) {
+            ws->partial_slots = 0;
+            ws->n_items = 0;
+            ws->overflow = 0;
+        }
+        if (t < kQueues) ws->cursor[t] = 0;
+        if (t < kNumClasses) {
+            ws->class_count[t] = 0;
+            ws->class_fill[t] = 0;
+        }
     }
 }
 
@@ -164,148 +157,238 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
     return v;
 }
 
-// Per cell: source count, exact pair total, and the demand of the base part length.
+// Per cell: source count; per box: exact pair total, unsplit items, and the sums that bound the partial slots
+// and items of a part length (slots <= n + slot_iters / length, items <= tiles + item_iters / length).  Also
+// clears the per-cell maxima of |a|^2 the force pass is about to record.  A workgroup walks its cells in
+// strides and adds its totals once: with one addition per wave the atomics on the one box of a large batch
+// dominated (late-time box of 4.2 million cells: 0.81 ms).
 __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs, const BoxDev *__restrict__ boxes,
                                                   int n_boxes, int64_t n_cells, int R, int S, int max_lanes,
-                                                  int32_t *__restrict__ cell_nsrc, WorkState *ws) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long inter = 0, pdem = 0, base_items = 0, split_items = 0;
-    if (c < n_cells) {
+                                                  int32_t *__restrict__ cell_nsrc,
+                                                  unsigned long long *__restrict__ amax, WorkBox *__restrict__ wb) {
+    __shared__ unsigned long long part[4][4];
+    unsigned long long v[4] = {0, 0, 0, 0};   // pairs, slot_iters, item_iters, tiles of the open box
+    int open = -1;
+    auto flush = [&]() {   // this thread's totals alone (a box boundary inside the workgroup's cells)
+        if (open >= 0 && v[3]) {
+            atomicAdd(&wb[open].pairs, v[0]);
+            atomicAdd(&wb[open].slot_iters, v[1]);
+            atomicAdd(&wb[open].item_iters, v[2]);
+            atomicAdd(&wb[open].tiles, v[3]);
+        }
+        v[0] = v[1] = v[2] = v[3] = 0;
+    };
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += (int64_t)gridDim.x * blockDim.x) {
         const int n = cs[c + 1] - cs[c];
         int nsrc = 0;
         if (n > 0) {
             const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
+            if (b != open) {
+                flush();
+                open = b;
+            }
             const BoxDev B = boxes[b];
             nsrc = cell_sources(cs, B, (int)(c - B.cell_base), R);
-            inter = (unsigned long long)n * (unsigned long long)nsrc;
-            const CellPlan p = plan_cell(n, nsrc, S, max_lanes, ws->part_iters);
-            base_items = (unsigned long long)p.tiles;
-            if (p.parts > 1) {
-                pdem = (unsigned long long)p.parts * (unsigned long long)n;
-                split_items = (unsigned long long)p.items;
-            }
+            const int tiles = tile_count(n, S, max_lanes), L0 = tile_at(n, S, max_lanes, 0).L;
+            const unsigned long long iters = (unsigned long long)((nsrc + L0 - 1) / L0);
+            v[0] += (unsigned long long)n * (unsigned long long)nsrc;
+            v[1] += (unsigned long long)n * iters;
+            v[2] += (unsigned long long)tiles * iters;
+            v[3] += (unsigned long long)tiles;
         }
         cell_nsrc[c] = nsrc;
+        if (amax) amax[c] = 0;
     }
-    inter = wave_sum_u64(inter);
-    pdem = wave_sum_u64(pdem);
-    base_items = wave_sum_u64(base_items);
-    split_items = wave_sum_u64(split_items);
-    if ((threadIdx.x & 63) == 0) {
-        if (inter) atomicAdd(&ws->interactions, inter);
-        if (pdem) atomicAdd(&ws->part_demand, pdem);
-        if (base_items) atomicAdd(&ws->base_items, base_items);
-        if (split_items) atomicAdd(&ws->split_items, split_items);
+    if (n_boxes > 1) {   // one addition per wave whose lanes ended in one box
+        const int first = __builtin_amdgcn_readfirstlane(open);
+        if (first >= 0 && __ballot(open == first) == ~0ull) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) v[q] = wave_sum_u64(v[q]);
+            if ((threadIdx.x & 63) != 0) open = -1;
+        }
+        flush();
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        v[q] = wave_sum_u64(v[q]);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][q] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int q = threadIdx.x;
+        const unsigned long long t = part[0][q] + part[1][q] + part[2][q] + part[3][q];
+        if (t) atomicAdd((q == 0 ? &wb[0].pairs : q == 1 ? &wb[0].slot_iters : q == 2 ? &wb[0].item_iters : &wb[0].tiles), t);
     }
 }
 
-// Lengthen the source parts until the partial slots and the items fit.
-__global__ void k_wl_plan(WorkState *ws, int64_t partial_capacity, int64_t item_capacity, int64_t n_total) {
-    if (threadIdx.x != 0) return;
-    const int64_t pbudget = partial_capacity - n_total;
-    const int64_t ibudget = item_capacity - (int64_t)ws->base_items;
-    int64_t f = 1;
-    const int64_t pd = (int64_t)ws->part_demand, id = (int64_t)ws->split_items;
-    if (pd > 0) {
-        int64_t fp = pbudget > 0 ? (pd + pbudget - 1) / pbudget : INT_MAX;
-        if (fp > f) f = fp;
+// Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
+// at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
+// leaves the rest of the chip idle until it ends.  The length follows from the box's own work alone, so a box
+// gives bit-identical forces whatever batch it is in.  It is at most the tuning's part_sources and at least
+// kMinPart, and every length is scaled up alike where partial slots or items would not fit.
+__global__ __launch_bounds__(256) void k_wl_plan(const WorkState *__restrict__ ws, WorkBox *__restrict__ wb, int n_boxes, int S,
+                                                 int part_sources, int64_t partial_capacity, int64_t item_capacity,
+                                                 int64_t n_total) {
+    __shared__ unsigned long long sum[3];   // slot and item bounds at the unscaled lengths, unsplit items
+    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
+    __syncthreads();
+    auto length = [&](const WorkBox &w) {
+        const unsigned long long fill = w.pairs / ((unsigned long long)(64 * S) * kFillItems);
+        const long long lo = kMinPart < part_sources ? kMinPart : part_sources;
+        const long long it = fill > (unsigned long long)part_sources ? part_sources : (long long)fill;
+        return it < lo ? lo : it;
+    };
+    unsigned long long slots = 0, items = 0, tiles = 0;
+    for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
+        const WorkBox w = wb[b];
+        const unsigned long long it = (unsigned long long)length(w);
+        slots += w.slot_iters / it + 1;
+        items += w.item_iters / it + 1;
+        tiles += w.tiles;
     }
-    if (id > 0) {
-        int64_t fi = ibudget > 0 ? (id + ibudget - 1) / ibudget : INT_MAX;
-        if (fi > f) f = fi;
+    if (tiles) {
+        atomicAdd(&sum[0], slots);
+        atomicAdd(&sum[1], items);
+        atomicAdd(&sum[2], tiles);
     }
-    int64_t it = (int64_t)ws->part_iters * f;
-    ws->part_iters = (int32_t)(it > INT_MAX ? INT_MAX : it);
+    __syncthreads();
+    const double pbudget = (double)(partial_capacity - n_total), ibudget = (double)item_capacity - (double)sum[2];
+    double f = 1.0;
+    if ((double)sum[0] > pbudget) f = pbudget >= 1.0 ? (double)sum[0] / pbudget : 1e18;
+    if ((double)sum[1] > ibudget) {
+        const double fi = ibudget >= 1.0 ? (double)sum[1] / ibudget : 1e18;
+        f = fi > f ? fi : f;
+    }
+    if (f > 1.0) f *= 1.0 + 1e-9;
+    for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
+        const double it = f > 1.0 ? ceil((double)length(wb[b]) * f) : (double)length(wb[b]);
+        wb[b].part_iters = it > (double)INT_MAX ? INT_MAX : (int32_t)it;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
-                                                  int64_t n_cells, int S, int max_lanes, WorkState *ws,
-                                                  int32_t *__restrict__ cell_parts, int64_t *__restrict__ cell_pdem) {
+                                                  const BoxDev *__restrict__ boxes, int n_boxes, int64_t n_cells, int S,
+                                                  int max_lanes, const WorkBox *__restrict__ wb, WorkState *ws,
+                                                  int32_t *__restrict__ cell_parts, int64_t *__restrict__ cell_pbase) {
     __shared__ int32_t hist[kNumClasses];
+    __shared__ unsigned long long need, base;   // partial slots of this workgroup's split cells
     if (threadIdx.x < kNumClasses) hist[threadIdx.x] = 0;
+    if (threadIdx.x == 0) need = 0;
     __syncthreads();
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int part_iters = ws->part_iters;
+    unsigned long long local = 0;
+    int parts = 0;
     if (c < n_cells) {
         const int n = cs[c + 1] - cs[c];
-        const CellPlan p = plan_cell(n, cell_nsrc[c], S, max_lanes, part_iters);
-        cell_parts[c] = p.parts;
-        cell_pdem[c] = p.parts > 1 ? (int64_t)p.parts * n : 0;
-        if (p.items > 0) atomicAdd(&hist[p.cls], (int32_t)p.items);
+        const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
+        const int nsrc = cell_nsrc[c];
+        parts = cell_part_count(n, nsrc, S, max_lanes, wb[b].part_iters);
+        cell_parts[c] = parts;
+        if (parts > 1) local = atomicAdd(&need, (unsigned long long)parts * (unsigned long long)n);
+        if (n > 0)
+            atomicAdd(&hist[cell_class(n, nsrc, S, max_lanes, parts)], tile_count(n, S, max_lanes) * parts);
     }
     __syncthreads();
+    if (threadIdx.x == 0) base = need ? atomicAdd(&ws->partial_slots, need) : 0;
     if (threadIdx.x < kNumClasses && hist[threadIdx.x]) atomicAdd(&ws->class_count[threadIdx.x], hist[threadIdx.x]);
+    __syncthreads();
+    if (parts > 1) cell_pbase[c] = (int64_t)(base + local);
 }
 
-__global__ void k_wl_classes(WorkState *ws, int64_t item_capacity, const int64_t *__restrict__ pbase,
-                             const int64_t *__restrict__ pdem, int64_t n_cells, int64_t partial_capacity,
-                             int *err) {
-    if (threadIdx.x != 0) return;
-    int64_t run = 0;
-    for (int k = 0; k < kNumClasses; k++) {
-        ws->class_base[k] = (int32_t)(run < INT_MAX ? run : INT_MAX);
-        ws->class_fill[k] = 0;
-        run += ws->class_count[k];
-    }
-    int64_t need_p = n_cells > 0 ? pbase[n_cells - 1] + pdem[n_cells - 1] : 0;
-    bool over = run > item_capacity || need_p > partial_capacity;
-    // on overflow nothing is emitted and nothing is computed: the error is
-    // reported by abacus_nf_sync and the output is left unwritten
-    ws->n_items = over ? 0 : (int32_t)run;
-    for (int q = 0; q < kQueues; q++) ws->cursor[q] = 0;
-    // slot j of queue x holds item ((j / kQueueBlock) * kQueues + x) * kQueueBlock + j % kQueueBlock, increasing
-    // in j: the first slot of each queue at or past the first light item
-    const int64_t L0 = ws->class_base[kLightClass];
-    const int64_t B = L0 / kQueueBlock, o = L0 % kQueueBlock;
-    for (int x = 0; x < kQueues; x++) {
-        const int64_t bq = B > x ? (B - x + kQueues - 1) / kQueues : 0;   // first block of queue x at or past B
-        const int64_t slot = bq * kQueueBlock + (bq * kQueues + x == B ? o : 0);
-        ws->light_slot[x] = (int32_t)(slot < INT_MAX ? slot : INT_MAX);
-    }
-    ws->overflow = over ? 1 : 0;
-    if (over) atomicCAS(err, 0, ABACUS_NF_ECAPACITY);
-}
-
+// Items in class order.  Every workgroup forms the class offsets (heaviest class first) from the counts; the
+// first one also records the item count, the capacity check and where the light items start in each queue.
 __global__ __launch_bounds__(256) void k_wl_emit(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
                                                  const int32_t *__restrict__ cell_parts,
                                                  const BoxDev *__restrict__ boxes, int n_boxes, int64_t n_cells,
-                                                 int S, int max_lanes, WorkState *ws, Item *__restrict__ items,
-                                                 int64_t item_capacity) {
+                                                 int S, int max_lanes, WorkState *ws,
+                                                 Item *__restrict__ items, int64_t item_capacity,
+                                                 int64_t partial_capacity, int *err) {
     __shared__ int32_t cnt[kNumClasses];
-    __shared__ int32_t bbase[kNumClasses];
-    if (threadIdx.x < kNumClasses) cnt[threadIdx.x] = 0;
+    __shared__ int64_t cbase[kNumClasses];
+    __shared__ int32_t over;
+    __shared__ int32_t end[256], ntile[256], cbox[256], wsum[4];
+    __shared__ int64_t first[256];
+    static_assert(kNumClasses == 64, "one lane per class");
+    if (threadIdx.x < kNumClasses) {
+        const int k = threadIdx.x;
+        cnt[k] = 0;
+        const int64_t own = ws->class_count[k];
+        int64_t incl = own;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t y = __shfl_up(incl, off);
+            if (k >= off) incl += y;
+        }
+        cbase[k] = incl - own;
+        const int64_t run = __shfl(incl, 63);
+        // on overflow nothing is emitted and nothing is computed: the error is
+        // reported by abacus_nf_sync and the output is left unwritten
+        const int o = run > item_capacity || (int64_t)ws->partial_slots > partial_capacity ? 1 : 0;
+        const int64_t L0 = __shfl(incl - own, kLightClass);
+        if (k == 0) over = o;
+        if (blockIdx.x == 0) {
+            if (k == 0) {
+                ws->n_items = o ? 0 : (int32_t)run;
+                ws->overflow = o;
+                if (o) atomicCAS(err, 0, ABACUS_NF_ECAPACITY);
+            }
+            // slot j of queue x holds item ((j / kQueueBlock) * kQueues + x) * kQueueBlock + j % kQueueBlock,
+            // increasing in j: the first slot of each queue at or past the first light item
+            const int64_t B = L0 / kQueueBlock, r = L0 % kQueueBlock;
+            if (k < kQueues) {
+                const int64_t bq = B > k ? (B - k + kQueues - 1) / kQueues : 0;   // first block of queue k at or past B
+                const int64_t slot = bq * kQueueBlock + (bq * kQueues + k == B ? r : 0);
+                ws->light_slot[k] = (int32_t)(slot < INT_MAX ? slot : INT_MAX);
+            }
+        }
+    }
     __syncthreads();
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    CellPlan p;
-    p.items = 0;
-    p.cls = 0;
-    p.tiles = p.parts = 0;
-    int local = 0;
-    if (c < n_cells) {
+    const int64_t c0 = (int64_t)blockIdx.x * blockDim.x, c = c0 + threadIdx.x;
+    int tiles = 0, parts = 0, cls = 0, local = 0, b = 0;
+    if (c < n_cells && !over) {
         const int n = cs[c + 1] - cs[c];
         if (n > 0) {
-            p = plan_cell(n, cell_nsrc[c], S, max_lanes, ws->part_iters);
-            p.parts = cell_parts[c];
-            p.items = (int64_t)p.tiles * p.parts;
-            local = atomicAdd(&cnt[p.cls], (int32_t)p.items);
+            b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
+            parts = cell_parts[c];
+            tiles = tile_count(n, S, max_lanes);
+            cls = cell_class(n, cell_nsrc[c], S, max_lanes, parts);
+            local = atomicAdd(&cnt[cls], tiles * parts);
         }
     }
     __syncthreads();
     if (threadIdx.x < kNumClasses) {
-        int k = threadIdx.x;
-        bbase[k] = cnt[k] ? atomicAdd(&ws->class_fill[k], cnt[k]) : 0;
+        const int k = threadIdx.x;
+        if (cnt[k]) cbase[k] += atomicAdd(&ws->class_fill[k], cnt[k]);
     }
     __syncthreads();
-    if (p.items > 0 && !ws->overflow) {
-        const int64_t base = (int64_t)ws->class_base[p.cls] + bbase[p.cls] + local;
-        if (base + p.items <= item_capacity) {
-            const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
-            // part-major: consecutive items are the tiles of one source part, so the waves that take them
-            // together (one queue block goes to one XCD) stream the same sources through that XCD's L2
-            int64_t k = base;
-            for (int q = 0; q < p.parts; q++)
-                for (int t = 0; t < p.tiles; t++) items[k++] = Item{(int32_t)c, t, q, b};
+    // The items of the workgroup's cells are written by all of its threads (a halo core alone has thousands),
+    // part-major within a cell: consecutive items are the tiles of one source part, so the waves that take them
+    // together (one queue block goes to one XCD) stream the same sources through that XCD's L2.
+    const int own = tiles * parts;
+    int incl = own;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(incl, off);
+        if ((int)(threadIdx.x & 63) >= off) incl += y;
+    }
+    if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < (int)(threadIdx.x >> 6); w++) before += wsum[w];
+    end[threadIdx.x] = before + incl;
+    first[threadIdx.x] = cbase[cls] + local;
+    ntile[threadIdx.x] = tiles;
+    cbox[threadIdx.x] = b;
+    __syncthreads();
+    const int total = end[255];
+    for (int i = threadIdx.x; i < total; i += 256) {
+        int lo = 0, hi = 255;   // the first cell whose items end past i
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (end[mid] > i) hi = mid; else lo = mid + 1;
         }
+        const int j = i - (lo > 0 ? end[lo - 1] : 0), nt = ntile[lo];
+        const int64_t k = first[lo] + j;
+        if (k < item_capacity) items[k] = Item{(int32_t)(c0 + lo), j % nt, j / nt, cbox[lo]};
     }
 }
 
@@ -383,8 +466,8 @@ __device__ inline double wave_max_f64(double v) {
 // while the others wait for theirs runs alone for a while (measured on a loop of these 12 operations: 48 clocks a
 // pair at six waves per SIMD).  So the reciprocal square roots of up to kGroupPairs pairs are issued together at
 // raised wave priority: once one wave has started, the others reach theirs before plain work goes on, and all
-// come out in step (33 clocks a pair in the same loop).  Clustered box of 256^3 particles, K = 64, compensated
-// sums: 112.9 -> 104.0 ms at two sinks per lane and two sources a step, 120.1 -> 99.9 at four sinks.
+// come out in step (33 clocks a pair in the same loop).  Clustered box of 256^3 particles, K = 64: 112.9 -> 99.9
+// ms (four sinks per lane, two sources a step; 104.0 ms with two sinks, 120.1 -> 99.9 at equal tiles).
 template <int KIND, int MODE, int S, int U, bool KDE>
 __device__ __forceinline__ void accumulate(const float4 (&p)[U], const float (&xi)[S], const float (&yi)[S],
                                            const float (&zi)[S], float c0, float c1, float c2, float e2,
@@ -753,12 +836,16 @@ __global__ __launch_bounds__(256) void k_finalize(const WorkState *__restrict__ 
     if (ws->overflow) return;
     const int lane = threadIdx.x & 63;
     int32_t c = -1;
+    int P = 0;
     double m = 0.0;   // |a|^2 written for this slot
     if (s < n) {
         c = keys[s];
-        const int P = cell_parts[c];
+        P = cell_parts[c];
+    }
+    if (!__ballot(P > 1)) return;   // most waves of a large box: no split cell
+    if (s < n) {
         const int cs0 = cs[c], nc = cs[c + 1] - cs0;
-        const int64_t base = cell_pbase[c] + (s - cs0);
+        const int64_t base = P > 1 ? cell_pbase[c] + (s - cs0) : 0;
         if (P > 1 && base + (int64_t)(P - 1) * nc < partial_capacity) {
             const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, c) : 0;
             const ForceBox F = fbox[b];
@@ -768,10 +855,12 @@ __global__ __launch_bounds__(256) void k_finalize(const WorkState *__restrict__ 
                 double v;   // the value before its (optional) rounding to FP32
                 if constexpr (MODE == ABACUS_NF_SUM_FP32) {
                     float t = 0.f;
+#pragma unroll 4
                     for (int p = 0; p < P; p++) t += (float)partials[NC * (base + (int64_t)p * nc) + d];
                     v = d < 3 ? t * F.scalef : t;
                 } else {
                     double t = 0.0;
+#pragma unroll 4
                     for (int p = 0; p < P; p++) t += partials[NC * (base + (int64_t)p * nc) + d];
                     v = d < 3 ? t * F.scale : t;
                 }
@@ -905,33 +994,31 @@ hipError_t launch_set_force_boxes(const double *eps, const double *gm, const dou
     return hipSuccess;
 }
 
-hipError_t launch_count_interactions(const ForcesArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL(k_wl_clear, dim3(1), dim3(kNumClasses), 0, st, a.ws, a.tune.part_sources);
+hipError_t launch_count_interactions(const ForcesArgs &a, bool clear_amax, hipStream_t st) {
+    hipLaunchKernelGGL(k_wl_clear, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.n_boxes);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_cells <= 0) return e;
-    hipLaunchKernelGGL(k_wl_cells, dim3(grid_for(a.n_cells, 256)), dim3(256), 0, st, a.cell_start, a.boxes,
-                       a.n_boxes, a.n_cells, a.R, a.tune.sinks_per_lane, a.tune.max_lanes, a.cell_nsrc, a.ws);
+    // at most 2048 workgroups (eight per CU), so that their additions to a box's totals stay few
+    const unsigned g = grid_for(a.n_cells, 256);
+    hipLaunchKernelGGL(k_wl_cells, dim3(g < 2048 ? g : 2048), dim3(256), 0, st, a.cell_start, a.boxes, a.n_boxes,
+                       a.n_cells, a.R, a.tune.sinks_per_lane, a.tune.max_lanes, a.cell_nsrc,
+                       clear_amax ? a.amax : nullptr, a.wb);
     return hipGetLastError();
 }
 
 hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
-    hipError_t e = launch_count_interactions(a, st);
+    hipError_t e = launch_count_interactions(a, true, st);
     if (e != hipSuccess || a.n_cells <= 0) return e;
-    if ((e = launch_fill_u64(a.amax, a.n_cells, 0ull, st)) != hipSuccess) return e;
     const int S = a.tune.sinks_per_lane, ML = a.tune.max_lanes;
     const unsigned gc = grid_for(a.n_cells, 256);
-    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(64), 0, st, a.ws, a.partial_capacity, a.item_capacity, a.n_total);
+    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(256), 0, st, a.ws, a.wb, a.n_boxes, S, a.tune.part_sources,
+                       a.partial_capacity, a.item_capacity, a.n_total);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wl_count, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.n_cells, S, ML, a.ws,
-                       a.cell_parts, a.cell_pdem);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = scan_i64_add_exclusive(a.cell_pdem, a.cell_pbase, a.n_cells, a.scan_temp, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wl_classes, dim3(1), dim3(64), 0, st, a.ws, a.item_capacity, a.cell_pbase, a.cell_pdem,
-                       a.n_cells, a.partial_capacity, a.err);
+    hipLaunchKernelGGL(k_wl_count, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
+                       a.n_cells, S, ML, a.wb, a.ws, a.cell_parts, a.cell_pbase);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_wl_emit, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.cell_parts, a.boxes,
-                       a.n_boxes, a.n_cells, S, ML, a.ws, a.items, a.item_capacity);
+                       a.n_boxes, a.n_cells, S, ML, a.ws, a.items, a.item_capacity, a.partial_capacity, a.err);
     return hipGetLastError();
 }
 

@@ -50,20 +50,33 @@ constexpr int kQueueBlock = 32;
 constexpr int kLightClass = 44;
 constexpr int kLightClaim = 8;
 
+// Source lists are split so that a box gives at least about kFillItems items of equal cost (four for each wave the
+// chip holds at four per SIMD), into parts of at least kMinPart source iterations per lane.  Measured (force kernel
+// and finalize, leapfrog case of 262144 particles / Plummer box of 1000003 / batch of 48 boxes, ms): 8192 items 2.04
+// / 5.9 / 4.4, 16384 2.04 / 5.6 / 4.4, 32768 2.02 / 5.6 / 4.5; unsplit 7.9 / 12.2 / 4.3.  Shorter parts than
+// kMinPart cost more in set-up, partial sums and their reading than they balance (the batch: 4.4 at 128, 4.2 at 256).
+constexpr unsigned long long kFillItems = 16384;
+constexpr long long kMinPart = 256;
+
+// Work of one box in a forces call.
+struct WorkBox {
+    unsigned long long pairs;       // sum over cells of n_c * sources(c)
+    unsigned long long slot_iters;  // sum of n_c * source iterations per lane of the cell's first tile
+    unsigned long long item_iters;  // sum of tiles * source iterations per lane
+    unsigned long long tiles;       // items with every source list unsplit
+    int32_t part_iters;             // part length (source iterations per lane)
+    int32_t pad;
+};
+
 // Device-side state of the work list of one forces call.
 struct WorkState {
-    unsigned long long interactions;  // sum over cells of n_c * sources(c)
-    unsigned long long part_demand;   // partial slots needed at the base part size
-    int32_t n_items;                  // items emitted (clamped to the capacity)
-    int32_t cursor[kQueues];          // next item of each queue of the persistent kernel
-    int32_t part_iters;               // effective part length (source iterations per lane)
+    unsigned long long partial_slots; // partial slots of the split cells
+    int32_t n_items;                  // items emitted (0 when a list outgrew its allocation)
+    int32_t cursor[kQueues];          // next slot of each queue of the persistent kernel
     int32_t overflow;                 // non-zero when a list outgrew its capacity
-    unsigned long long base_items;    // items with every source list unsplit
-    unsigned long long split_items;   // items of cells whose source list is split
     int32_t class_count[kNumClasses];
     int32_t class_fill[kNumClasses];
-    int32_t class_base[kNumClasses];
-    int32_t light_slot[kQueues];       // first slot of each queue that holds a light item
+    int32_t light_slot[kQueues];      // first slot of each queue that holds a light item
 };
 
 // Sink tiles of one cell.  The n sinks form g = ceil(n / S) groups of S (one
@@ -180,7 +193,6 @@ hipError_t radix_sort_pairs(int32_t *keys, int32_t *vals, int32_t *keys_tmp, int
                             int32_t **vals_out);
 size_t scan_temp_bytes(int64_t n);
 hipError_t scan_i32_max_inclusive(const int32_t *in, int32_t *out, int64_t n, void *temp, hipStream_t st);
-hipError_t scan_i64_add_exclusive(const int64_t *in, int64_t *out, int64_t n, void *temp, hipStream_t st);
 hipError_t launch_cell_start(const int32_t *keys_sorted, int64_t n, int64_t n_cells, int32_t *endpos,
                              int32_t *cell_start, void *scan_temp, hipStream_t st);
 hipError_t launch_gather(const float *pos, const int32_t *perm, const int32_t *keys_sorted, int64_t n,
@@ -217,10 +229,10 @@ struct ForcesArgs {
     Item *items;
     int64_t item_capacity;
     WorkState *ws;
+    WorkBox *wb;        // [n_boxes]
     int32_t *cell_nsrc;
     int32_t *cell_parts;
-    int64_t *cell_pdem;
-    int64_t *cell_pbase;
+    int64_t *cell_pbase;   // first partial slot of a split cell (unset for others)
     double *partials;
     int64_t partial_capacity;
     float *acc;
@@ -232,7 +244,6 @@ struct ForcesArgs {
     abacus_nf_sum mode;
     abacus_nf_tuning tune;
     int grid;        // persistent-kernel workgroups
-    void *scan_temp;
 };
 
 hipError_t launch_set_force_boxes(const double *eps, const double *gm, const double *kde_b, abacus_nf_kind kind,
@@ -241,7 +252,8 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st);
 hipError_t launch_forces(const ForcesArgs &a, hipStream_t st);
 hipError_t launch_finalize(const ForcesArgs &a, hipStream_t st);
 int forces_grid(const abacus_nf_tuning &t, abacus_nf_kind kind, abacus_nf_sum mode, bool kde, int device);
-hipError_t launch_count_interactions(const ForcesArgs &a, hipStream_t st);
+// Fills wb[b].pairs of every box (and the totals the work list is planned from).
+hipError_t launch_count_interactions(const ForcesArgs &a, bool clear_amax, hipStream_t st);
 
 // Leapfrog time stepping (kdk.hip)
 hipError_t upload_box_doubles(const double *host, int n_boxes, double *dev, hipStream_t st);
