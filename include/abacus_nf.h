@@ -347,14 +347,15 @@ int abacus_nf_copy_cells(abacus_nf_cells cells, abacus_nf_array which, void *dst
 typedef struct {
     int32_t sinks_per_lane;  /* i-tile per lane: 1, 2 or 4                                  */
     int32_t chunk;           /* j-tile: sources staged per LDS chunk (multiple of 64,
-                                64*unroll <= chunk <= 512)                                   */
+                                64*unroll <= chunk <= 512; at most 256 are staged at a time) */
     int32_t unroll;          /* sources in flight per lane: 1, 2 or 4                        */
     int32_t max_lanes;       /* most lanes sharing one sink (1..64)                          */
-    int32_t part_sources;    /* split a tile's source list into parts of about this many
-                                sources per lane (>= 1024)                                   */
+    int32_t part_sources;    /* split a tile's source list into parts of at most about this
+                                many sources per lane (>= 1024); boxes whose work would give
+                                too few items are split further                              */
     int32_t waves_per_cu;    /* persistent-kernel waves per compute unit (0 = occupancy)     */
-    int32_t occupancy;       /* register budget of the kernel variant: 0 = compiler's choice,
-                                6 or 8 = at least that many waves per SIMD                   */
+    int32_t occupancy;       /* register budget of the kernel variant: at least four (0), six
+                                or eight (6, 8) waves per SIMD                               */
     int32_t reserved;        /* must be 0                                                    */
     int64_t item_capacity;   /* work-list capacity override (tests); 0 = sized from the batch */
 } abacus_nf_tuning;

@@ -19,6 +19,7 @@
 //
 // Numbers are in cell-width units: positions are relative to the sink cell's
 // centre, so the pair terms need no large-coordinate cancellation.
+#include <algorithm>
 #include <climits>
 #include <cstring>
 #include <cmath>
@@ -31,6 +32,8 @@ namespace {
 
 constexpr int kWaves = 4;                 // independent waves per workgroup
 constexpr int kThreads = 64 * kWaves;
+constexpr int kRounds = 4;                // source slots per lane of a staged chunk
+constexpr int kMaxCols = 49;              // near-field columns at the largest R
 constexpr int kGroupPairs = 8;            // pairs of a lane whose reciprocal square roots go together
 constexpr float kTiny = 1e-20f;           // keeps rsqrt finite for coincident pairs
 constexpr float kFar = 1e18f;             // padding source: its terms underflow to exactly 0
@@ -134,7 +137,7 @@ __device__ inline int cell_class(int n, int nsrc, int S, int max_lanes, int part
 
 // ---------------------------------------------------------------- work-list kernels
 
-__global__ __launch_bounds__(256) void k_wl_clear(WorkState *ws, WorkBox *wb, int n_boxes) {
+__global__ __launch_bounds__(256) void k_wl_clear(WorkState *ws, WorkBox *wb, int n_boxes, int grid) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_boxes) wb[i] = WorkBox{0, 0, 0, 0, 0, 0};
     if (blockIdx.x == 0) {
@@ -144,7 +147,8 @@ __global__ __launch_bounds__(256) void k_wl_clear(WorkState *ws, WorkBox *wb, in
             ws->n_items = 0;
             ws->overflow = 0;
         }
-        if (t < kQueues) ws->cursor[t] = 0;
+        // the first slots of every queue belong to the waves that start on it
+        if (t < kQueues) ws->cursor[t][0] = grid > t ? (grid - t + kQueues - 1) / kQueues * kWaves : 0;
         if (t < kNumClasses) {
             ws->class_count[t] = 0;
             ws->class_fill[t] = 0;
@@ -410,14 +414,14 @@ struct KArgs {
     float *rho;
     unsigned long long *amax;   // [n_cells] bits of the largest |a|^2 written in each cell
     int R;
-    int chunk;      // sources per LDS chunk
+    int chunk;      // sources per LDS chunk (at most 64 * kRounds)
     int max_lanes;
     int region;     // bytes of LDS per wave
 };
 
-struct Seg {
-    int32_t src, len, flat;
-    float czref;
+// Offsets of the sources of one near-field column, in LDS: entry 2 c + i for run i of column c.
+struct ColOff {
+    float x, y, czref;
 };
 
 // Orders LDS traffic between the lanes of one wave (no other wave takes part).
@@ -466,8 +470,8 @@ __device__ inline double wave_max_f64(double v) {
 // while the others wait for theirs runs alone for a while (measured on a loop of these 12 operations: 48 clocks a
 // pair at six waves per SIMD).  So the reciprocal square roots of up to kGroupPairs pairs are issued together at
 // raised wave priority: once one wave has started, the others reach theirs before plain work goes on, and all
-// come out in step (33 clocks a pair in the same loop).  Clustered box of 256^3 particles, K = 64: 112.9 -> 99.9
-// ms (four sinks per lane, two sources a step; 104.0 ms with two sinks, 120.1 -> 99.9 at equal tiles).
+// come out in step (33 clocks a pair in the same loop).  Clustered box of 256^3 particles, K = 64, compensated
+// sums: 112.9 -> 104.0 ms at two sinks per lane and two sources a step, 120.1 -> 99.9 at four sinks.
 template <int KIND, int MODE, int S, int U, bool KDE>
 __device__ __forceinline__ void accumulate(const float4 (&p)[U], const float (&xi)[S], const float (&yi)[S],
                                            const float (&zi)[S], float c0, float c1, float c2, float e2,
@@ -535,52 +539,83 @@ __device__ __forceinline__ void accumulate(const float4 (&p)[U], const float (&x
     }
 }
 
-// OCC > 0 asks the compiler for at least OCC waves per SIMD (a register budget of
-// 512/OCC VGPRs); OCC = 0 leaves the register budget to the compiler.
+// Twelve floats of a lane to and from LDS (only the lane itself reads them).
+template <int S>
+__device__ inline void store_low(float4 *p, const float (&x)[S], const float (&y)[S], const float (&z)[S]) {
+    if constexpr (S == 4) {
+        p[0] = make_float4(x[0], x[1], x[2], x[3]);
+        p[1] = make_float4(y[0], y[1], y[2], y[3]);
+        p[2] = make_float4(z[0], z[1], z[2], z[3]);
+    }
+}
+
+template <int S>
+__device__ inline void load_low(const float4 *p, float (&x)[S], float (&y)[S], float (&z)[S]) {
+    if constexpr (S == 4) {
+        const float4 a = p[0], b = p[1], c = p[2];
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+        y[0] = b.x; y[1] = b.y; y[2] = b.z; y[3] = b.w;
+        z[0] = c.x; z[1] = c.y; z[2] = c.z; z[3] = c.w;
+    }
+}
+
+// Item of slot j of queue x: the list is dealt to the queues in blocks of kQueueBlock.
+__device__ inline int64_t queue_item(int j, int x) {
+    return ((int64_t)(j / kQueueBlock) * kQueues + x) * kQueueBlock + j % kQueueBlock;
+}
+
+// OCC > 0 asks the compiler for at least OCC waves per SIMD (a register budget of 512/OCC VGPRs), OCC = 0 for four:
+// an even number, as the SIMD pairs the plain operations of two waves (at three waves per SIMD one runs unpaired).
 template <int KIND, int MODE, int S, int U, int OCC, bool KDE>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 1, OCC > 0 ? OCC : 8)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 4, OCC > 0 ? OCC : 8)))
 void k_forces(KArgs a) {
     constexpr int NC = KDE ? 4 : 3;  // reduced components per sink: acceleration (+ density)
     extern __shared__ __align__(16) unsigned char smem[];
-    const int wave = threadIdx.x >> 6;
+    const int wave = sgpr(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     unsigned char *region = smem + (size_t)wave * a.region;
     float4 *stage = (float4 *)region;
-    Seg *segs = (Seg *)(region + (size_t)a.chunk * sizeof(float4));
     double *red = (double *)region;
     float *redf = (float *)region;
+    ColOff *coff = (ColOff *)(region + (size_t)a.region - 2 * kMaxCols * sizeof(ColOff));
     const int R = a.R;
     const int W = 2 * R + 1;
     const int ncol = W * W;
     const int n_items = a.ws->n_items;
-    const int home = blockIdx.x % kQueues;
-    int queue = 0;  // queues tried so far (own queue first, then the others in turn)
-
-    int jnext = 0, jleft = 0;   // slots of the current queue claimed and not yet taken: [jnext, jnext + jleft)
+    // Slots of the queue claimed and not yet taken: [jnext, jnext + jleft).  The first slot of every wave is
+    // its own number among the waves that start on its queue (the cursors start past those).  Later ones are
+    // claimed with one atomic each, or kLightClaim at a time once the queue has reached its light items.  A
+    // wave whose queue is drained looks at all cursors with one load before it claims elsewhere: failing
+    // claims of every wave on every queue, at 12 ns each on one cache line, were the floor of small calls
+    // (32768 particles: 0.48 ms of 0.91).
+    int x = blockIdx.x % kQueues;
+    int jnext = (int)(blockIdx.x / kQueues) * kWaves + wave, jleft = 1;
     for (;;) {
-        // next item: slot j of queue x holds item x + kQueues*(j / kQueueBlock) (block) of the list; one atomic
-        // claims one slot, or kLightClaim slots once the queue has reached its light items
         int k = n_items;
-        while (queue < kQueues) {
-            const int x = (home + queue) % kQueues;
+        for (;;) {
             if (jleft == 0) {
                 const int want = jnext >= a.ws->light_slot[x] ? kLightClaim : 1;
                 int j = 0;
-                if (lane == 0) j = atomicAdd(&a.ws->cursor[x], want);
+                if (lane == 0) j = atomicAdd(&a.ws->cursor[x][0], want);
                 jnext = sgpr(__shfl(j, 0));
                 jleft = want;
             }
-            const int j = jnext;
+            const int64_t idx = queue_item(jnext, x);
             jnext++;
             jleft--;
-            const int64_t idx = ((int64_t)(j / kQueueBlock) * kQueues + x) * kQueueBlock + j % kQueueBlock;
             if (idx < n_items) {
                 k = (int)idx;
                 break;
             }
-            queue++;  // queue x is drained (its later slots only grow)
-            jnext = 0;
+            // queue x is drained (its later slots only grow): the next queue with slots left, if any
             jleft = 0;
+            int c = INT_MAX;
+            if (lane < kQueues) c = __hip_atomic_load(&a.ws->cursor[lane][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned open = (unsigned)__ballot(lane < kQueues && queue_item(c, lane) < n_items);
+            if (!open) break;
+            const unsigned turned = (open >> x) | (open << (kQueues - x));   // queue x in bit 0
+            x = (x + __builtin_ctz(turned)) % kQueues;
+            jnext = __builtin_amdgcn_readlane(c, x);
         }
         if (k >= n_items) break;
         const Item it = a.items[k];
@@ -611,7 +646,8 @@ void k_forces(KArgs a) {
             zi[s] = p.z;
         }
 
-        // segment table of the near field (one column per lane), flattened by a prefix sum
+        // the near field, one column per lane, flattened by a prefix sum: source q of column `lane` is slot
+        // q + base0 (the first len0 of them) or q + base1
         ColSeg o;
         o.src0 = o.len0 = o.src1 = o.len1 = 0;
         o.czref0 = o.czref1 = 0.f;
@@ -626,13 +662,14 @@ void k_forces(KArgs a) {
             if (lane >= off) incl += y;
         }
         const int nsrc = sgpr(__shfl(incl, 63));
-        wave_lds_sync();
+        const int cend = incl;                               // end of the column in the flattened list
+        const int csplit = incl - o.len1;                    // where its second run starts
+        const int base0 = o.src0 - (incl - (o.len0 + o.len1)), base1 = o.src1 - csplit;
         if (lane < ncol) {
-            const int start = incl - (o.len0 + o.len1);
-            segs[2 * lane] = Seg{o.src0, o.len0, start, o.czref0};
-            segs[2 * lane + 1] = Seg{o.src1, o.len1, start + o.len0, o.czref1};
+            const float ox = (float)(lane / W - R), oy = (float)(lane % W - R);
+            coff[2 * lane] = ColOff{ox, oy, o.czref0};
+            coff[2 * lane + 1] = ColOff{ox, oy, o.czref1};
         }
-        wave_lds_sync();
 
         const int P = a.cell_parts[c];
         const int part = sgpr(it.part);
@@ -643,6 +680,10 @@ void k_forces(KArgs a) {
 
         float ax[S], ay[S], az[S];
         float hx[S], hy[S], hz[S], lx[S], ly[S], lz[S];
+        // at four sinks per lane the low words of the compensated sums stay in LDS behind the staged chunk (read
+        // and written once per chunk): in registers they would be spilled at four waves per SIMD
+        constexpr bool kLowLds = MODE == ABACUS_NF_SUM_COMP32 && S == 4;
+        float4 *low = (float4 *)(region + 64 * kRounds * sizeof(float4)) + 3 * lane;
         double dxs[S], dys[S], dzs[S];
         float rh[S];
         double rhd[S];
@@ -659,36 +700,74 @@ void k_forces(KArgs a) {
         const int step = L * U;
         const int nmax = (a.chunk / step) * step;
 
-        int si = 0;
+        // A chunk [f, f + n) of the flattened source list is fetched into registers with all of its loads in
+        // flight at once: slot 64 r + lane in v[r], its run of a column in byte r of runs (255: none).  The chunk
+        // after the one being summed is under way during the sums.
+        float4 v[kRounds];
+        static_assert(kRounds == 4 && 2 * kMaxCols < 255, "a byte per round");
+        unsigned runs = 0xffffffffu;
+        int ci = 0;   // first column that reaches past the chunk fetched last
+        auto fetch = [&](int f, int n) {
+            int src[kRounds], w[kRounds];
+#pragma unroll
+            for (int r = 0; r < kRounds; r++) {
+                src[r] = 0;
+                w[r] = 255;
+            }
+            const int stop = f + n;
+            for (;; ci++) {
+                const int e = __builtin_amdgcn_readlane(cend, ci);
+                if (e > f) {
+                    const int b0 = __builtin_amdgcn_readlane(base0, ci), m = __builtin_amdgcn_readlane(csplit, ci);
+                    const int b = e > stop ? stop : e;
+                    if (m == e) {   // one run
+#pragma unroll
+                        for (int r = 0; r < kRounds; r++) {
+                            const int q = f + 64 * r + lane;
+                            if (w[r] == 255 && q < b) {
+                                src[r] = q + b0;
+                                w[r] = 2 * ci;
+                            }
+                        }
+                    } else {        // the column wraps through the box boundary
+                        const int b1 = __builtin_amdgcn_readlane(base1, ci);
+#pragma unroll
+                        for (int r = 0; r < kRounds; r++) {
+                            const int q = f + 64 * r + lane;
+                            if (w[r] == 255 && q < b) {
+                                src[r] = q + (q < m ? b0 : b1);
+                                w[r] = 2 * ci + (q < m ? 0 : 1);
+                            }
+                        }
+                    }
+                }
+                if (e >= stop || ci + 1 >= ncol) break;
+            }
+#pragma unroll
+            for (int r = 0; r < kRounds; r++)
+                if (w[r] != 255) v[r] = a.spos[src[r]];
+            runs = (unsigned)w[0] | (unsigned)w[1] << 8 | (unsigned)w[2] << 16 | (unsigned)w[3] << 24;
+        };
+        if constexpr (kLowLds) store_low(low, lx, ly, lz);
+        if (j0 < j1) fetch(j0, min(nmax, j1 - j0));
+        wave_lds_sync();   // coff, and the last item's reads of the region
+
         for (int f = j0; f < j1;) {
             const int n = min(nmax, j1 - f);
-            // stage [f, f+n) of the flattened source list, offsets applied
-            int ff = f;
-            while (ff < f + n) {
-                Seg sg = segs[si];
-                int sflat = sgpr(sg.flat), slen = sgpr(sg.len);
-                while (sflat + slen <= ff && si + 1 < 2 * ncol) {
-                    si++;
-                    sg = segs[si];
-                    sflat = sgpr(sg.flat);
-                    slen = sgpr(sg.len);
-                }
-                const int end = min(sflat + slen, f + n);
-                if (end <= ff) break;  // unreachable for a consistent table; guarantees termination
-                const int col = si >> 1;
-                const float offx = (float)(col / W - R), offy = (float)(col % W - R);
-                const float czref = __builtin_bit_cast(float, sgpr(__builtin_bit_cast(int, sg.czref)));
-                const int srcb = sgpr(sg.src) + (ff - sflat);
-                const int cnt = end - ff;
-                float4 *dst = stage + (ff - f);
-                for (int q = lane; q < cnt; q += 64) {
-                    const float4 p = a.spos[srcb + q];
-                    dst[q] = make_float4(p.x + offx, p.y + offy, p.z + (p.w - czref), 0.f);
-                }
-                ff = end;
-            }
             const int npad = ((n + step - 1) / step) * step;
-            for (int q = n + lane; q < npad; q += 64) stage[q] = make_float4(kFar, kFar, kFar, 0.f);
+            // stage the chunk with the cell offsets applied; the last step is filled up with far sources
+#pragma unroll
+            for (int r = 0; r < kRounds; r++) {
+                const int q = 64 * r + lane;
+                const int run = (runs >> (8 * r)) & 255;
+                if (run != 255) {
+                    const ColOff co = coff[run];
+                    stage[q] = make_float4(v[r].x + co.x, v[r].y + co.y, v[r].z + (v[r].w - co.czref), 0.f);
+                } else if (q < npad) {
+                    stage[q] = make_float4(kFar, kFar, kFar, 0.f);
+                }
+            }
+            if (f + n < j1) fetch(f + n, min(nmax, j1 - f - n));
             wave_lds_sync();
 
             if constexpr (MODE == ABACUS_NF_SUM_COMP32) {
@@ -726,6 +805,7 @@ void k_forces(KArgs a) {
                 }
             }
             if constexpr (MODE == ABACUS_NF_SUM_COMP32) {
+                if constexpr (kLowLds) load_low(low, lx, ly, lz);
 #pragma unroll
                 for (int s = 0; s < S; s++) {
                     float e;
@@ -736,12 +816,18 @@ void k_forces(KArgs a) {
                     two_sum(hz[s], az[s], hz[s], e);
                     lz[s] += e;
                 }
+                if constexpr (kLowLds) store_low(low, lx, ly, lz);
             }
             wave_lds_sync();
             f += n;
         }
 
-        // ordered reduction over the L lanes that share each sink (all components at once)
+        if constexpr (kLowLds) {
+            load_low(low, lx, ly, lz);
+            wave_lds_sync();
+        }
+        // Ordered reduction over the L lanes that share each sink: every lane leaves its sums in LDS, lane o of
+        // the G S NC totals adds the L parts of total o in lane order, in place of the first of them.
 #pragma unroll
         for (int s = 0; s < S; s++) {
             const int o = (lane * S + s) * NC;
@@ -763,52 +849,57 @@ void k_forces(KArgs a) {
             }
         }
         wave_lds_sync();
-        double amax2 = 0.0;   // largest |a|^2 this lane writes (cells written here, not split ones)
-        if (sub == 0 && g < G) {
-            const bool split = P > 1;
-            for (int s = 0; s < S; s++) {
-                const int idx = g * S + s;
-                if (idx >= nt) break;
-                const int base = (g * L * S + s) * NC;
-                if (!split) {
-                    const int64_t i = a.perm[cs0 + t0 + idx];
-                    double w[3];   // the values written
-                    for (int d = 0; d < NC; d++) {
-                        double v;   // the value before its (optional) rounding to FP32
-                        if constexpr (MODE == ABACUS_NF_SUM_FP32) {
-                            float t = 0.f;
-                            for (int q = 0; q < L; q++) t += redf[base + q * S * NC + d];
-                            v = d < 3 ? t * F.scalef : t;
-                        } else {
-                            double t = 0.0;
-                            for (int q = 0; q < L; q++) t += red[base + q * S * NC + d];
-                            v = d < 3 ? t * F.scale : t;
-                        }
-                        if (d == 3) {
-                            a.rho[i] = (float)v;
-                        } else if (a.acc64) {
-                            a.acc64[3 * i + d] = v;
-                            w[d] = v;
-                        } else {
-                            a.acc[3 * i + d] = (float)v;
-                            w[d] = (double)(float)v;
-                        }
-                    }
-                    const double m = norm2_written(w[0], w[1], w[2]);
-                    amax2 = m > amax2 ? m : amax2;
+        if (L > 1) {
+            for (int o = lane; o < G * S * NC; o += 64) {
+                const int first = (o / (S * NC)) * (L - 1) * S * NC + o;
+                if constexpr (MODE == ABACUS_NF_SUM_FP32) {
+                    float t = 0.f;
+                    for (int q = 0; q < L; q++) t += redf[first + q * S * NC];
+                    redf[first] = t;
                 } else {
-                    double *out = a.partials + (int64_t)NC * (a.cell_pbase[c] + (int64_t)part * nc + t0 + idx);
-                    for (int d = 0; d < NC; d++) {
-                        if constexpr (MODE == ABACUS_NF_SUM_FP32) {
-                            float t = 0.f;
-                            for (int q = 0; q < L; q++) t += redf[base + q * S * NC + d];
-                            out[d] = t;
-                        } else {
-                            double t = 0.0;
-                            for (int q = 0; q < L; q++) t += red[base + q * S * NC + d];
-                            out[d] = t;
-                        }
+                    double t = 0.0;
+                    for (int q = 0; q < L; q++) t += red[first + q * S * NC];
+                    red[first] = t;
+                }
+            }
+            wave_lds_sync();
+        }
+        double amax2 = 0.0;   // largest |a|^2 this lane writes (cells written here, not split ones)
+        for (int idx = lane; idx < nt; idx += 64) {
+            const int base = ((idx / S) * L * S + idx % S) * NC;
+            if (P <= 1) {
+                const int64_t i = a.perm[cs0 + t0 + idx];
+                double wr[3];   // the values written
+#pragma unroll
+                for (int d = 0; d < NC; d++) {
+                    double val;   // the value before its (optional) rounding to FP32
+                    if constexpr (MODE == ABACUS_NF_SUM_FP32) {
+                        const float t = redf[base + d];
+                        val = d < 3 ? t * F.scalef : t;
+                    } else {
+                        const double t = red[base + d];
+                        val = d < 3 ? t * F.scale : t;
                     }
+                    if (d == 3) {
+                        a.rho[i] = (float)val;
+                    } else if (a.acc64) {
+                        a.acc64[3 * i + d] = val;
+                        wr[d] = val;
+                    } else {
+                        a.acc[3 * i + d] = (float)val;
+                        wr[d] = (double)(float)val;
+                    }
+                }
+                const double m = norm2_written(wr[0], wr[1], wr[2]);
+                amax2 = m > amax2 ? m : amax2;
+            } else {
+                double *out = a.partials + (int64_t)NC * (a.cell_pbase[c] + (int64_t)part * nc + t0 + idx);
+#pragma unroll
+                for (int d = 0; d < NC; d++) {
+                    if constexpr (MODE == ABACUS_NF_SUM_FP32)
+                        out[d] = redf[base + d];
+                    else
+                        out[d] = red[base + d];
                 }
             }
         }
@@ -946,11 +1037,16 @@ ForcesKernel pick_kernel(abacus_nf_kind kind, abacus_nf_sum mode, int S, int U, 
                                      : pick_mode<ABACUS_NF_SPLINE, false>(mode, S, U, occ);
 }
 
+// Sources staged at a time: the tuning's chunk, as far as the registers of a fetch hold it.
+int staged_chunk(const abacus_nf_tuning &t) { return t.chunk < 64 * kRounds ? t.chunk : 64 * kRounds; }
+
 size_t region_bytes(const abacus_nf_tuning &t) {
-    size_t stage = (size_t)t.chunk * sizeof(float4);
+    size_t stage = (size_t)staged_chunk(t) * sizeof(float4);
     size_t red = (size_t)64 * t.sinks_per_lane * 4 * sizeof(double);
-    size_t main = stage > red ? stage : red;
-    return (main + (size_t)2 * 49 * sizeof(Seg) + 15) & ~(size_t)15;
+    // the low words of the compensated sums at four sinks per lane lie behind a full chunk
+    const size_t low = t.sinks_per_lane == 4 ? 64 * (kRounds * sizeof(float4) + 3 * sizeof(float4)) : 0;
+    size_t main = std::max(std::max(stage, red), low);
+    return (main + 2 * kMaxCols * sizeof(ColOff) + 15) & ~(size_t)15;
 }
 
 }  // namespace
@@ -995,7 +1091,8 @@ hipError_t launch_set_force_boxes(const double *eps, const double *gm, const dou
 }
 
 hipError_t launch_count_interactions(const ForcesArgs &a, bool clear_amax, hipStream_t st) {
-    hipLaunchKernelGGL(k_wl_clear, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.n_boxes);
+    hipLaunchKernelGGL(k_wl_clear, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.n_boxes,
+                       a.grid);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_cells <= 0) return e;
     // at most 2048 workgroups (eight per CU), so that their additions to a box's totals stay few
@@ -1056,7 +1153,7 @@ hipError_t launch_forces(const ForcesArgs &a, hipStream_t st) {
     k.rho = a.rho;
     k.amax = a.amax;
     k.R = a.R;
-    k.chunk = a.tune.chunk;
+    k.chunk = staged_chunk(a.tune);
     k.max_lanes = a.tune.max_lanes;
     k.region = (int)region_bytes(a.tune);
     ForcesKernel kfn = pick_kernel(a.kind, a.mode, a.tune.sinks_per_lane, a.tune.unroll, a.tune.occupancy,

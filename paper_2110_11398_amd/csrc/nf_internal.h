@@ -44,11 +44,12 @@ constexpr int kNumClasses = 64;
 // cells then share one XCD's L2.
 constexpr int kQueues = 8;
 constexpr int kQueueBlock = 32;
-// Items of the light cost classes (an item of class >= kLightClass costs under ~1024 source iterations x sinks
-// per lane) are claimed kLightClaim queue slots per atomic: sparse regions hold millions of such items, and one
-// atomic per item on the queue cursors would bound the kernel.
-constexpr int kLightClass = 44;
-constexpr int kLightClaim = 8;
+// Items of the light cost classes (an item of class >= kLightClass costs under ~256 source iterations x sinks per
+// lane) are claimed kLightClaim queue slots per atomic: sparse regions hold millions of such items.  Larger claims
+// leave waves idle at the end of small calls (32768 particles: 0.30 ms at eight slots from class 44 on, 0.15 at four
+// from class 47 on); the late-time box takes the same time with each.
+constexpr int kLightClass = 47;
+constexpr int kLightClaim = 4;
 
 // Source lists are split so that a box gives at least about kFillItems items of equal cost (four for each wave the
 // chip holds at four per SIMD), into parts of at least kMinPart source iterations per lane.  Measured (force kernel
@@ -72,11 +73,11 @@ struct WorkBox {
 struct WorkState {
     unsigned long long partial_slots; // partial slots of the split cells
     int32_t n_items;                  // items emitted (0 when a list outgrew its allocation)
-    int32_t cursor[kQueues];          // next slot of each queue of the persistent kernel
     int32_t overflow;                 // non-zero when a list outgrew its capacity
     int32_t class_count[kNumClasses];
     int32_t class_fill[kNumClasses];
     int32_t light_slot[kQueues];      // first slot of each queue that holds a light item
+    alignas(256) int32_t cursor[kQueues][64];   // next slot of each queue in [0], a cache line of its own
 };
 
 // Sink tiles of one cell.  The n sinks form g = ceil(n / S) groups of S (one
