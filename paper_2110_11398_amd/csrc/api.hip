@@ -24,9 +24,9 @@ struct abacus_nf_cells_s {
 
     // capacities (elements)
     int64_t cap_n = -1, cap_cells = -1, cap_boxes = -1;
-    int32_t *keys_a = nullptr, *vals_a = nullptr, *keys_b = nullptr, *vals_b = nullptr;
-    int32_t *keys = nullptr, *perm = nullptr;  // sorted results (point into the buffers above)
-    float4 *spos = nullptr;
+    int32_t *keys_a = nullptr, *keys_b = nullptr, *perm = nullptr;
+    int32_t *keys = nullptr;                   // sorted keys (one of the buffers above)
+    float4 *spos = nullptr, *pay = nullptr;   // sorted coordinates; partitioned ones during a build
     int32_t *cell_start = nullptr;
     int32_t *endpos = nullptr;
     void *radix_temp = nullptr;
@@ -108,12 +108,12 @@ bool dalloc_bytes(void *&p, size_t bytes) {
 }
 
 void free_sort_buffers(abacus_nf_cells_s *h) {
-    dfree(h->keys_a); dfree(h->vals_a); dfree(h->keys_b); dfree(h->vals_b);
-    dfree(h->spos); dfree(h->cell_start); dfree(h->endpos); dfree(h->d_boxes); dfree(h->d_mass);
+    dfree(h->keys_a); dfree(h->keys_b); dfree(h->perm);
+    dfree(h->spos); dfree(h->pay); dfree(h->cell_start); dfree(h->endpos); dfree(h->d_boxes); dfree(h->d_mass);
     if (h->radix_temp) hipFree(h->radix_temp);
     if (h->scan_temp) hipFree(h->scan_temp);
     h->radix_temp = h->scan_temp = nullptr;
-    h->keys = h->perm = nullptr;
+    h->keys = nullptr;
     h->cap_n = h->cap_cells = h->cap_boxes = -1;
 }
 
@@ -288,10 +288,10 @@ int abacus_nf_build_cells(const float *pos, int64_t n_total, const abacus_nf_box
     if (h->cap_n < n || h->cap_cells < cells_total || h->cap_boxes < n_boxes) {
         free_sort_buffers(h);
         const int64_t cn = std::max<int64_t>(n, 1), cc = std::max<int64_t>(cells_total, 1);
-        bool ok = dalloc(h->keys_a, cn) && dalloc(h->vals_a, cn) && dalloc(h->keys_b, cn) &&
-                  dalloc(h->vals_b, cn) && dalloc(h->spos, cn) && dalloc(h->cell_start, cc + 1) &&
+        bool ok = dalloc(h->keys_a, cn) && dalloc(h->keys_b, cn) && dalloc(h->perm, cn) && dalloc(h->spos, cn) && dalloc(h->pay, cn) &&
+                  dalloc(h->cell_start, cc + 1) &&
                   dalloc(h->endpos, cc) && dalloc(h->d_boxes, n_boxes) && dalloc(h->d_mass, n_boxes) &&
-                  dalloc_bytes(h->radix_temp, radix_temp_bytes(cn)) &&
+                  dalloc_bytes(h->radix_temp, sort_temp_bytes(cn, key_bits(cc))) &&
                   dalloc_bytes(h->scan_temp, scan_temp_bytes(std::max(cc, cn)));
         if (!ok) {
             free_sort_buffers(h);
@@ -315,17 +315,27 @@ int abacus_nf_build_cells(const float *pos, int64_t n_total, const abacus_nf_box
     // ---- enqueue
     mark(h, 0, false, st);
     hipError_t e = launch_set_boxes(boxes, n_boxes, base.data(), h->d_boxes, st);
-    if (e == hipSuccess) e = launch_bin(pos, n, h->d_boxes, n_boxes, h->keys_a, h->vals_a, err, st);
-    int32_t *ks = h->keys_a, *vs = h->vals_a;
-    if (e == hipSuccess)
-        e = radix_sort_pairs(h->keys_a, h->vals_a, h->keys_b, h->vals_b, h->radix_temp, n, key_bits(cells_total), st,
-                             &ks, &vs);
-    if (e == hipSuccess) e = launch_cell_start(ks, n, cells_total, h->endpos, h->cell_start, h->scan_temp, st);
-    if (e == hipSuccess) e = launch_gather(pos, vs, ks, n, h->d_boxes, n_boxes, h->spos, st);
+    int32_t *ks = h->keys_a;
+    bool starts = false;
+    SortArgs sa;
+    sa.pos = pos;
+    sa.n = n;
+    sa.n_cells = cells_total;
+    sa.boxes = h->d_boxes;
+    sa.n_boxes = n_boxes;
+    sa.keys_a = h->keys_a;
+    sa.keys_b = h->keys_b;
+    sa.perm = h->perm;
+    sa.pay = h->pay;
+    sa.spos = h->spos;
+    sa.cell_start = h->cell_start;
+    sa.temp = h->radix_temp;
+    sa.err = err;
+    if (e == hipSuccess) e = sort_by_cell(sa, key_bits(cells_total), &ks, &starts, st);
+    if (e == hipSuccess && !starts) e = launch_cell_start(ks, n, cells_total, h->endpos, h->cell_start, h->scan_temp, st);
     if (e != hipSuccess) return hip_fail(e);
     mark(h, 0, true, st);
     h->keys = ks;
-    h->perm = vs;
     h->built = true;
     return ABACUS_NF_OK;
 }

@@ -1,5 +1,5 @@
-// Cell construction for the near-field force: binning, a stable LSD radix sort
-// of particles by cell, the cell offsets, and the cell-relative FP32 layout.
+// Cell construction for the near-field force: binning, a stable sort of the
+// particles by cell, the cell offsets, and the cell-relative FP32 layout.
 //
 // Sec. 3.1 of the paper cuts each periodic box into a cubic lattice of CPD^3
 // cells; the near field of a particle is defined by the cells around its own.
@@ -7,15 +7,25 @@
 // GPU every step (Table "tbl:timing": "Transpose Positions", "Merge New
 // Particles").  Here the equivalent is done on the device, in HBM:
 //
-//   k_bin            cell of every particle (FP64 cell rule), key/value pairs
-//   k_radix_hist     per-tile digit histograms of the keys          } one pass per
-//   scan             exclusive scan of the (digit, tile) counts      } 8-bit digit,
-//   k_radix_scatter  stable scatter (wave ballots rank equal digits) } LSD order
-//   k_run_ends       end slot of every non-empty cell; a max-scan turns those
-//                    into the cell offsets (empty cells inherit the previous end)
-//   k_gather         cell-relative coordinates in cell widths, FP64 -> FP32
+//   k_bin          cell of every particle (FP64 cell rule) and a tile histogram of its leading digit
+//   k_seg_scatter  as partition: stable scatter by the leading digit (up to 8 bits) of coordinates, input index and
+//                  cell; every later step then works inside one bucket, whose few MB stay in cache
+//   k_seg_hist,    per bucket: digit counts of every tile, their exclusive sums over the tiles and the digits
+//   k_seg_scan
+//   k_seg_scatter  stable scatter inside the buckets; the last one writes the sorted keys, the permutation and
+//                  the cell-relative coordinates in cell widths, FP64 -> FP32
+//
+// Where the last digit spans the whole cell index inside a bucket (keys of up to 19 bits in large calls), its sums
+// are the cell offsets; longer keys take one more digit before it, and k_run_ends with a max-scan the offsets.
+// Small calls skip the partition: one bucket, one digit.
+//
+// Bound by memory: coordinates move in order three times (44 bytes read and 44 written per particle with the keys),
+// against one random 12-byte gather, a cache line each, when only keys and indices were sorted.  Clustered box of
+// 16.7 million particles in random order 866 -> 600 us, late-time box of 33.5 million 2006 -> 1570, 6 million 358 ->
+// 205, 2 million 154 -> 95.
 //
 // Every step is deterministic: particles of a cell stay in input order.
+#include <algorithm>
 #include <cstring>
 
 #include "nf_internal.h"
@@ -26,7 +36,7 @@ namespace {
 
 constexpr int kTileThreads = 256;
 constexpr int kTileItems = 16;
-constexpr int kTile = kTileThreads * kTileItems;  // 4096 elements per workgroup
+constexpr int kTile = kTileThreads * kTileItems;  // elements per workgroup of a scan
 
 inline unsigned grid_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
@@ -52,8 +62,12 @@ __global__ void k_set_boxes(BoxChunk c, BoxDev *dst) {
 //   xt = x - L*floor(x/L),  t = xt*s (s = K/L),  c = min(floor(t), K-1).
 __device__ inline int axis_cell(double x, double L, double s, int K, double *t_out) {
 #pragma clang fp contract(off)
-    double q = floor(x / L);
-    double xt = x - L * q;
+    // x / L rounds below 1 for x up to L (1 - 2^-50): floor is 0 and xt is x, without the division
+    double xt = x;
+    if (!(x >= 0.0 && x < L * (1.0 - 0x1p-50))) {
+        double q = floor(x / L);
+        xt = x - L * q;
+    }
     double t = xt * s;
     double f = floor(t);
     int c = (f >= (double)(K - 1)) ? (K - 1) : (int)f;
@@ -62,26 +76,46 @@ __device__ inline int axis_cell(double x, double L, double s, int K, double *t_o
     return c;
 }
 
-__global__ __launch_bounds__(256) void k_bin(const float *__restrict__ pos, int64_t n,
-                                             const BoxDev *__restrict__ boxes, int n_boxes,
-                                             int32_t *__restrict__ keys, int32_t *__restrict__ vals, int *err) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int b = n_boxes > 1 ? box_of_particle(boxes, n_boxes, i) : 0;
-    const BoxDev B = boxes[b];
-    double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
-    int32_t key = B.cell_base;
-    if (isfinite(x) && isfinite(y) && isfinite(z)) {
-        double t;
-        int cx = axis_cell(x, B.L, B.s, B.K, &t);
-        int cy = axis_cell(y, B.L, B.s, B.K, &t);
-        int cz = axis_cell(z, B.L, B.s, B.K, &t);
-        key = B.cell_base + (cx * B.K + cy) * B.K + cz;
-    } else {
-        atomicCAS(err, 0, ABACUS_NF_ENONFINITE);
+// Cell of every particle of a tile, and the tile's histogram of bits [shift, shift + bits) of the cell index:
+// row `tile` of hist when by_row, else column `tile` ([digit][tile], for one scan over all of it).
+template <int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_bin(const float *__restrict__ pos, int64_t n,
+                                                 const BoxDev *__restrict__ boxes, int n_boxes,
+                                                 int32_t *__restrict__ keys, int shift, int bits,
+                                                 uint32_t *__restrict__ hist, int by_row, int *err) {
+    extern __shared__ uint32_t smem_u32[];
+    uint32_t *h = smem_u32;
+    const int D = 1 << bits, tid = threadIdx.x;
+    for (int d = tid; d < D; d += THREADS) h[d] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * (THREADS * ITEMS);
+#pragma unroll 4
+    for (int r = 0; r < ITEMS; r++) {
+        const int64_t i = base + r * THREADS + tid;
+        if (i >= n) break;
+        const int b = n_boxes > 1 ? box_of_particle(boxes, n_boxes, i) : 0;
+        const BoxDev B = boxes[b];
+        const double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
+        int32_t key = B.cell_base;
+        if (isfinite(x) && isfinite(y) && isfinite(z)) {
+            double t;
+            const int cx = axis_cell(x, B.L, B.s, B.K, &t);
+            const int cy = axis_cell(y, B.L, B.s, B.K, &t);
+            const int cz = axis_cell(z, B.L, B.s, B.K, &t);
+            key = B.cell_base + (cx * B.K + cy) * B.K + cz;
+        } else {
+            atomicCAS(err, 0, ABACUS_NF_ENONFINITE);
+        }
+        keys[i] = key;
+        atomicAdd(&h[((uint32_t)key >> shift) & (uint32_t)(D - 1)], 1u);
     }
-    keys[i] = key;
-    vals[i] = (int32_t)i;
+    __syncthreads();
+    for (int d = tid; d < D; d += THREADS) {
+        if (by_row)
+            hist[(int64_t)blockIdx.x * D + d] = h[d];
+        else
+            hist[(int64_t)d * gridDim.x + blockIdx.x] = h[d];
+    }
 }
 
 // ---------------------------------------------------------------- scans
@@ -170,135 +204,333 @@ hipError_t scan_impl(const T *in, T *out, int64_t n, bool inclusive, T identity,
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- radix sort
+// ---------------------------------------------------------------- sort by cell
 
-constexpr int kRadixMaxBits = 8;
-constexpr int kRadixBins = 1 << kRadixMaxBits;
-constexpr int kWaveSpan = kTile / 4;  // contiguous elements handled by one wave of a tile
+constexpr int kPartBits = 8;                 // most bits of the leading digit
+constexpr int kMaxBuckets = 1 << kPartBits;
+constexpr int kLastBits = 12;                 // most bits of a digit inside a bucket
+constexpr int kLastBitsBig = 11;              // the same in large calls (sixteen waves' counts in LDS)
 
-__global__ __launch_bounds__(kTileThreads) void k_radix_hist(const int32_t *__restrict__ keys, int64_t n, int shift,
-                                                             int bits, uint32_t *__restrict__ thist, int ntiles) {
-    __shared__ uint32_t h[kRadixBins];
-    int tid = threadIdx.x;
-    h[tid] = 0;
-    __syncthreads();
-    int64_t base = (int64_t)blockIdx.x * kTile;
-    uint32_t mask = (1u << bits) - 1u;
-#pragma unroll 4
-    for (int k = 0; k < kTileItems; k++) {
-        int64_t i = base + (int64_t)k * kTileThreads + tid;
-        if (i < n) atomicAdd(&h[((uint32_t)keys[i] >> shift) & mask], 1u);
+// Buckets of the partitioned order and the tiles they are cut into: bucket b is slots [start[b], start[b + 1]) and
+// tiles [tile[b], tile[b + 1]); an empty bucket has one (empty) tile.
+struct Buckets {
+    uint32_t start[kMaxBuckets + 1];
+    int32_t tile[kMaxBuckets + 1];
+};
+
+__global__ __launch_bounds__(kMaxBuckets) void k_buckets(const uint32_t *__restrict__ toff, int ntiles, int nb, int64_t n,
+                                                         int tile, Buckets *__restrict__ o) {
+    __shared__ int32_t wsum[kMaxBuckets / 64];
+    const int b = threadIdx.x, lane = b & 63;
+    const uint32_t lo = b < nb ? toff[(int64_t)b * ntiles] : (uint32_t)n;
+    const uint32_t hi = b + 1 < nb ? toff[(int64_t)(b + 1) * ntiles] : (uint32_t)n;
+    const int t = b < nb ? (hi > lo ? (int)((hi - lo + tile - 1) / tile) : 1) : 0;
+    int incl = t;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
     }
+    if (lane == 63) wsum[b >> 6] = incl;
     __syncthreads();
-    if (tid < (1 << bits)) thist[(int64_t)tid * ntiles + blockIdx.x] = h[tid];
+    for (int w = 0; w < (b >> 6); w++) incl += wsum[w];
+    o->start[b] = lo;
+    o->tile[b] = incl - t;
+    if (b == kMaxBuckets - 1) {
+        o->start[kMaxBuckets] = (uint32_t)n;
+        o->tile[kMaxBuckets] = incl;
+    }
 }
 
-// Stable scatter of one tile.  Wave w owns the contiguous span
-// [tile + w*1024, tile + (w+1)*1024), read in 16 rounds of 64.  Within a
-// round, lanes with equal digits are found with one ballot per digit bit; a
-// lane's rank is the number of equal lanes below it plus the wave's running
-// count of that digit.  Wave counts are then prefix-summed across the four
-// waves, and the tile's digit totals across the digits: every element gets
-// its position in the tile sorted by digit (input order within a digit).  The
-// tile is staged in LDS in that order and written out by consecutive threads,
-// so each digit's run goes to global memory in whole, contiguous pieces at
-// the tile's global offset for the digit (from the scanned (digit, tile)
-// histogram).
-__global__ __launch_bounds__(kTileThreads) void k_radix_scatter(const int32_t *__restrict__ kin,
-                                                                const int32_t *__restrict__ vin,
-                                                                int32_t *__restrict__ kout,
-                                                                int32_t *__restrict__ vout, int64_t n, int shift,
-                                                                int bits, const uint32_t *__restrict__ toff,
-                                                                int ntiles) {
-    static_assert(kTileThreads == kRadixBins, "one thread per digit in the per-digit steps");
-    __shared__ uint32_t wcnt[4][kRadixBins];
-    __shared__ uint32_t goff[kRadixBins];
-    __shared__ uint32_t loff[kRadixBins];
-    __shared__ int32_t skey[kTile];
-    __shared__ int32_t sval[kTile];
-    int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int d = tid; d < 4 * kRadixBins; d += kTileThreads) (&wcnt[0][0])[d] = 0;
-    if (tid < (1 << bits)) goff[tid] = toff[(int64_t)tid * ntiles + blockIdx.x];
+// Bucket, first slot and number of slots of tile g (bk null: one bucket of n slots); false past the last tile.
+__device__ inline bool seg_tile(const Buckets *__restrict__ bk, int64_t n, int tile, int g, int &bucket, int64_t &base,
+                                int &count) {
+    bucket = 0;
+    int64_t end = n;
+    base = (int64_t)g * tile;
+    if (bk) {
+        if (g >= bk->tile[kMaxBuckets]) return false;
+        int lo = 0, hi = kMaxBuckets - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (bk->tile[mid] <= g) lo = mid; else hi = mid - 1;
+        }
+        bucket = lo;
+        base = (int64_t)bk->start[lo] + (int64_t)(g - bk->tile[lo]) * tile;
+        end = bk->start[lo + 1];
+    }
+    const int64_t left = end - base;
+    count = left < tile ? (left > 0 ? (int)left : 0) : tile;
+    return true;
+}
+
+template <int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_seg_hist(const int32_t *__restrict__ keys, int64_t n,
+                                                      const Buckets *__restrict__ bk, int shift, int bits,
+                                                      uint32_t *__restrict__ rows) {
+    extern __shared__ uint32_t smem_u32[];
+    uint32_t *h = smem_u32;
+    int bucket, count;
+    int64_t base;
+    if (!seg_tile(bk, n, THREADS * ITEMS, blockIdx.x, bucket, base, count)) return;
+    const int D = 1 << bits, tid = threadIdx.x;
+    for (int d = tid; d < D; d += THREADS) h[d] = 0;
     __syncthreads();
-    const uint32_t mask = (1u << bits) - 1u;
-    const uint64_t below_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t tile = (int64_t)blockIdx.x * kTile;
-    const int64_t base = tile + (int64_t)w * kWaveSpan;
-    int32_t key[kTileItems], val[kTileItems];
-    uint32_t rank[kTileItems];
+#pragma unroll 4
+    for (int r = 0; r < ITEMS; r++) {
+        const int i = r * THREADS + tid;
+        if (i < count) atomicAdd(&h[((uint32_t)keys[base + i] >> shift) & (uint32_t)(D - 1)], 1u);
+    }
+    __syncthreads();
+    for (int d = tid; d < D; d += THREADS) rows[(int64_t)blockIdx.x * D + d] = h[d];
+}
+
+// One workgroup per bucket: the rows of its tiles become exclusive sums over the tiles, four digits to a thread and
+// the loads of eight rows in flight, and dbase the first slot of every digit.  With cell_start, bits that end the
+// key: slot of every cell.
+constexpr int kSegScanThreads = 1 << (kLastBits - 2);
+__global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(uint32_t *__restrict__ rows, uint32_t *__restrict__ dbase,
+                                                              const Buckets *__restrict__ bk, int64_t n, int ntiles,
+                                                              int bits, int32_t *__restrict__ cell_start,
+                                                              int64_t n_cells) {
+    __shared__ uint32_t wsum[kSegScanThreads / 64];
+    const int Q = 1 << (bits - 2), tid = threadIdx.x, b = blockIdx.x, lane = tid & 63;   // Q groups of four digits
+    const int t0 = bk ? bk->tile[b] : 0, t1 = bk ? bk->tile[b + 1] : ntiles;
+    uint4 run = make_uint4(0, 0, 0, 0);   // then the totals of this thread's digits
+    auto add = [](uint4 &x, const uint4 &y) {
+        x.x += y.x;
+        x.y += y.y;
+        x.z += y.z;
+        x.w += y.w;
+    };
+    if (tid < Q) {
+        uint4 *col = (uint4 *)rows + (int64_t)t0 * Q + tid;
+        int t = t0;
+        for (; t + 8 <= t1; t += 8, col += 8 * (int64_t)Q) {
+            uint4 v[8];
 #pragma unroll
-    for (int r = 0; r < kTileItems; r++) {
-        int64_t i = base + (int64_t)r * 64 + lane;
-        bool valid = i < n;
-        key[r] = valid ? kin[i] : 0;
-        val[r] = valid ? vin[i] : 0;
-        uint32_t d = ((uint32_t)key[r] >> shift) & mask;
+            for (int q = 0; q < 8; q++) v[q] = col[q * (int64_t)Q];
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                col[q * (int64_t)Q] = run;
+                add(run, v[q]);
+            }
+        }
+        for (; t < t1; t++, col += Q) {
+            const uint4 v = *col;
+            *col = run;
+            add(run, v);
+        }
+    }
+    const uint32_t s = run.x + run.y + run.z + run.w;
+    uint32_t incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) wsum[tid >> 6] = incl;
+    __syncthreads();
+    if (tid < Q) {
+        uint32_t first = (bk ? bk->start[b] : 0u) + incl - s;
+        for (int w = 0; w < (tid >> 6); w++) first += wsum[w];
+        const uint4 o = make_uint4(first, first + run.x, first + run.x + run.y, first + run.x + run.y + run.z);
+        const int64_t g = (int64_t)b * Q + tid;
+        ((uint4 *)dbase)[g] = o;
+        if (cell_start) {
+            const uint32_t v[4] = {o.x, o.y, o.z, o.w};
+            for (int q = 0; q < 4; q++)
+                if (4 * g + q < n_cells) cell_start[4 * g + q] = (int32_t)v[q];
+        }
+    }
+    if (cell_start && b == 0 && tid == 0) cell_start[n_cells] = (int32_t)n;
+}
+
+// What a scatter reads and writes.
+enum SegOut {
+    kSegPart,      // positions by input index -> coordinates with their input index
+    kSegMid,       // coordinates with their input index -> the same
+    kSegLastPos,   // positions by input index -> the sorted layout
+    kSegLast       // coordinates with their input index -> the sorted layout
+};
+
+struct SegArgs {
+    const int32_t *kin;
+    const float *pos;            // kSegPart, kSegLastPos
+    const float4 *pay;           // kSegMid, kSegLast: x, y, z, input index (bits)
+    const uint32_t *rows;        // per tile and digit: first slot among the digit's (kSegPart: absolute, [digit][tile])
+    const uint32_t *dbase;       // per bucket and digit: first slot
+    const Buckets *bk;
+    const BoxDev *boxes;
+    int n_boxes;
+    int64_t n;
+    int shift, bits;
+    int32_t *kout;
+    int32_t *vout;               // last scatter: permutation
+    float4 *out;                 // coordinates, or spos in the last scatter
+};
+
+constexpr int kStageMost = 2048;   // elements staged in LDS at a time
+
+// spos = (t_x - (c_x + 1/2), t_y - (c_y + 1/2), t_z - (c_z + 1/2), c_z) where t = xt*K/L is the wrapped
+// coordinate in cell widths: positions relative to the centre of their own cell, in cell widths, rounded once to
+// FP32.
+__device__ inline float4 cell_relative(float px, float py, float pz, const BoxDev &B) {
+    const double x = px, y = py, z = pz;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (isfinite(x) && isfinite(y) && isfinite(z)) {
+        double tx, ty, tz;
+        const int cx = axis_cell(x, B.L, B.s, B.K, &tx);
+        const int cy = axis_cell(y, B.L, B.s, B.K, &ty);
+        const int cz = axis_cell(z, B.L, B.s, B.K, &tz);
+        o.x = (float)(tx - ((double)cx + 0.5));
+        o.y = (float)(ty - ((double)cy + 0.5));
+        o.z = (float)(tz - ((double)cz + 0.5));
+        o.w = (float)cz;
+    }
+    return o;
+}
+
+// Stable scatter of one tile.  Wave w owns the contiguous span [w * 64 ITEMS, (w + 1) * 64 ITEMS) of the tile, read
+// in ITEMS rounds of 64.  Within a round, lanes with equal digits are found with one ballot per digit bit; a lane's
+// rank is the number of equal lanes below it plus the wave's running count of that digit.  Wave counts are then
+// prefix-summed across the waves and the tile's digit totals across the digits: every element gets its position in
+// the tile sorted by digit.  The elements wait in registers (read in order) and go through LDS in that order, 2048
+// positions at a time, so that consecutive threads write consecutive elements of a run.  (With element numbers
+// staged instead, and the elements read from the tile in sorted order, every lane touched a cache line of its own:
+// 16.7 million particles 333 + 486 us for the two scatters.)
+template <int THREADS, int ITEMS, int OUT>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 1024 ? 8 : 4))) void k_seg_scatter(SegArgs a) {
+    constexpr int TILE = THREADS * ITEMS, WAVES = THREADS / 64, STAGE = TILE < kStageMost ? TILE : kStageMost;
+    extern __shared__ __align__(16) uint32_t smem_u32[];
+    const int D = 1 << a.bits;
+    float4 *stage = (float4 *)smem_u32;                   // [STAGE] x, y, z, input index
+    int32_t *skey = (int32_t *)(stage + STAGE);           // [STAGE]
+    uint32_t *gd = (uint32_t *)(skey + STAGE);            // [D] global slot of a digit's run minus its tile position
+    uint32_t *wsum = gd + D;                              // [WAVES]
+    uint16_t *wcnt = (uint16_t *)(wsum + WAVES);          // [WAVES][D] counts, then tile positions
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    int bucket, count;
+    int64_t base;
+    if (!seg_tile(OUT == kSegPart || OUT == kSegLastPos ? nullptr : a.bk, a.n, TILE, blockIdx.x, bucket, base, count))
+        return;
+    for (int d = tid; d < WAVES * D / 2; d += THREADS) ((uint32_t *)wcnt)[d] = 0;
+    __syncthreads();
+    const uint32_t mask = (uint32_t)(D - 1);
+    const uint64_t below_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const uint32_t span = w * 64 * ITEMS + lane, un = (uint32_t)count;   // this thread's elements: span + 64 r
+    const int32_t *kin = a.kin + base;
+    uint32_t dig[ITEMS];   // digit, and the rank above it; then the position in the sorted tile
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
+        const uint32_t i = span + r * 64;
+        dig[r] = i < un ? ((uint32_t)kin[i] >> a.shift) & mask : 0u;
+    }
+    // the elements themselves: on their way while the ranks are formed
+    constexpr bool kFromPos = OUT == kSegPart || OUT == kSegLastPos;
+    float ex[ITEMS], ey[ITEMS], ez[ITEMS];
+    int32_t ei[kFromPos ? 1 : ITEMS];
+    const float *pos = kFromPos ? a.pos + 3 * base : nullptr;
+    const float4 *pay = kFromPos ? nullptr : a.pay + base;
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
+        const uint32_t i = span + r * 64;
+        ex[r] = ey[r] = ez[r] = 0.f;
+        if constexpr (!kFromPos) ei[r] = 0;
+        if (i < un) {
+            if constexpr (kFromPos) {
+                ex[r] = pos[3 * i];
+                ey[r] = pos[3 * i + 1];
+                ez[r] = pos[3 * i + 2];
+            } else {
+                const float4 v = pay[i];
+                ex[r] = v.x;
+                ey[r] = v.y;
+                ez[r] = v.z;
+                ei[r] = __float_as_int(v.w);
+            }
+        }
+    }
+    uint16_t *wc = wcnt + w * D;
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
+        const bool valid = span + r * 64 < un;
+        const uint32_t d = dig[r];
         uint64_t m = __ballot(valid);
-        for (int b = 0; b < bits; b++) {
-            int bit = (d >> b) & 1u;
-            uint64_t bb = __ballot(bit);
+        for (int b = 0; b < a.bits; b++) {
+            const int bit = (d >> b) & 1u;
+            const uint64_t bb = __ballot(bit);
             m &= bit ? bb : ~bb;
         }
-        uint32_t below = (uint32_t)__popcll(m & below_mask);
-        uint32_t cnt = (uint32_t)__popcll(m);
-        uint32_t c0 = valid ? wcnt[w][d] : 0u;
-        rank[r] = c0 + below;
-        if (valid && below == 0) wcnt[w][d] = c0 + cnt;
+        const uint32_t below = (uint32_t)__popcll(m & below_mask);
+        const uint32_t c0 = valid ? wc[d] : 0u;
+        if (valid && below == 0) wc[d] = (uint16_t)(c0 + (uint32_t)__popcll(m));
+        dig[r] = d | (c0 + below) << 16;
     }
     __syncthreads();
-    {
-        // digit tid: prefix over the waves, and the tile's total
-        uint32_t run = 0;
-        for (int w2 = 0; w2 < 4; w2++) {
-            uint32_t c = wcnt[w2][tid];
-            wcnt[w2][tid] = run;
-            run += c;
-        }
-        loff[tid] = run;
+    // tile positions: exclusive sums over the digits (`per` consecutive ones a thread), then over the waves
+    const int per = (D + THREADS - 1) / THREADS;
+    uint32_t s = 0;
+    for (int q = 0; q < per; q++) {
+        const int d = tid * per + q;
+        if (d < D)
+            for (int v = 0; v < WAVES; v++) s += wcnt[v * D + d];
     }
-    __syncthreads();
-    if (w == 0) {
-        // exclusive scan of the tile's digit totals: four digits per lane, then a wave scan of the lane sums
-        uint32_t v[4], s = 0;
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            v[q] = s;
-            s += loff[4 * lane + q];
-        }
-        uint32_t incl = s;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = __shfl_up(incl, off);
-            if (lane >= off) incl += y;
-        }
-        const uint32_t excl = incl - s;
-#pragma unroll
-        for (int q = 0; q < 4; q++) loff[4 * lane + q] = excl + v[q];
+    uint32_t incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
     }
+    if (lane == 63) wsum[w] = incl;
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kTileItems; r++) {
-        int64_t i = base + (int64_t)r * 64 + lane;
-        if (i < n) {
-            const uint32_t d = ((uint32_t)key[r] >> shift) & mask;
-            const uint32_t lp = loff[d] + wcnt[w][d] + rank[r];
-            skey[lp] = key[r];
-            sval[lp] = val[r];
+    uint32_t run = incl - s;
+    for (int v = 0; v < w; v++) run += wsum[v];
+    for (int q = 0; q < per; q++) {
+        const int d = tid * per + q;
+        if (d < D) {
+            const uint32_t first = OUT == kSegPart ? a.rows[(int64_t)d * gridDim.x + blockIdx.x]
+                                                   : a.rows[(int64_t)blockIdx.x * D + d] + a.dbase[(int64_t)bucket * D + d];
+            gd[d] = first - run;
+            for (int v = 0; v < WAVES; v++) {
+                const uint32_t c = wcnt[v * D + d];
+                wcnt[v * D + d] = (uint16_t)run;
+                run += c;
+            }
         }
     }
     __syncthreads();
-    const int64_t left = n - tile;
-    const int tile_n = left < kTile ? (int)left : kTile;
-#pragma unroll 4
-    for (int j = 0; j < kTileItems; j++) {
-        const int lp = j * kTileThreads + tid;
-        if (lp < tile_n) {
-            const int32_t k = skey[lp];
-            const uint32_t d = ((uint32_t)k >> shift) & mask;
-            const uint32_t dest = goff[d] + ((uint32_t)lp - loff[d]);
-            kout[dest] = k;
-            vout[dest] = sval[lp];
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
+        dig[r] = span + r * 64 < un ? wc[dig[r] & 0xffffu] + (dig[r] >> 16) : 0xffffffffu;
+    }
+    for (int c0 = 0; c0 < count; c0 += STAGE) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; r++) {
+            const uint32_t q = dig[r] - (uint32_t)c0;
+            if (q < (uint32_t)STAGE) {
+                const uint32_t i = span + r * 64;
+                const int32_t from = kFromPos ? (int32_t)base + (int32_t)i : ei[kFromPos ? 0 : r];
+                stage[q] = make_float4(ex[r], ey[r], ez[r], __int_as_float(from));
+                skey[q] = kin[i];
+            }
         }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < STAGE / THREADS; r++) {
+            const int q = r * THREADS + tid;
+            if (c0 + q < count) {
+                const int32_t k = skey[q];
+                const float4 v = stage[q];
+                const uint32_t dest = gd[((uint32_t)k >> a.shift) & mask] + (uint32_t)(c0 + q);
+                a.kout[dest] = k;
+                if constexpr (OUT == kSegPart || OUT == kSegMid) {
+                    a.out[dest] = v;
+                } else {
+                    const int b = a.n_boxes > 1 ? box_of_cell(a.boxes, a.n_boxes, k) : 0;
+                    a.out[dest] = cell_relative(v.x, v.y, v.z, a.boxes[b]);
+                    a.vout[dest] = __float_as_int(v.w);
+                }
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -309,33 +541,6 @@ __global__ void k_run_ends(const int32_t *__restrict__ keys, int64_t n, int32_t 
     if (s >= n) return;
     int32_t k = keys[s];
     if (s == n - 1 || keys[s + 1] != k) endpos[k] = (int32_t)(s + 1);
-}
-
-// spos[s] = (t_x - (c_x + 1/2), t_y - (c_y + 1/2), t_z - (c_z + 1/2), c_z) where
-// t = xt*K/L is the wrapped coordinate in cell widths: positions relative to
-// the centre of their own cell, in cell widths, rounded once to FP32.
-__global__ __launch_bounds__(256) void k_gather(const float *__restrict__ pos, const int32_t *__restrict__ perm,
-                                                const int32_t *__restrict__ keys, int64_t n,
-                                                const BoxDev *__restrict__ boxes, int n_boxes,
-                                                float4 *__restrict__ spos) {
-    int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    int64_t i = perm[s];
-    int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, keys[s]) : 0;
-    const BoxDev B = boxes[b];
-    double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (isfinite(x) && isfinite(y) && isfinite(z)) {
-        double tx, ty, tz;
-        int cx = axis_cell(x, B.L, B.s, B.K, &tx);
-        int cy = axis_cell(y, B.L, B.s, B.K, &ty);
-        int cz = axis_cell(z, B.L, B.s, B.K, &tz);
-        o.x = (float)(tx - ((double)cx + 0.5));
-        o.y = (float)(ty - ((double)cy + 0.5));
-        o.z = (float)(tz - ((double)cz + 0.5));
-        o.w = (float)cz;
-    }
-    spos[s] = o;
 }
 
 }  // namespace
@@ -371,58 +576,167 @@ hipError_t launch_set_boxes(const abacus_nf_box *boxes, int n_boxes, const int32
     return hipSuccess;
 }
 
-hipError_t launch_bin(const float *pos, int64_t n, const BoxDev *boxes, int n_boxes, int32_t *keys, int32_t *vals,
-                      int *err, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bin, dim3(grid_for(n, 256)), dim3(256), 0, st, pos, n, boxes, n_boxes, keys, vals, err);
-    return hipGetLastError();
-}
-
 size_t scan_temp_bytes(int64_t n) { return scan_levels_bytes(n, sizeof(int64_t)) + 1024; }
 
 hipError_t scan_i32_max_inclusive(const int32_t *in, int32_t *out, int64_t n, void *temp, hipStream_t st) {
     return scan_impl<int32_t, OpMax>(in, out, n, true, (int32_t)0, (char *)temp, st);
 }
 
-size_t radix_temp_bytes(int64_t n) {
-    int64_t ntiles = (n + kTile - 1) / kTile;
-    int64_t hist = ntiles * kRadixBins;
-    return 2 * (size_t)hist * sizeof(uint32_t) + scan_levels_bytes(hist, sizeof(uint32_t)) + 1024;
+namespace {
+
+// Tiles: 4096 elements in large calls, four to a thread, so that two workgroups of sixteen waves fit a CU (build of
+// the clustered box of 16.7 million particles: 607 us; 512 threads with eight elements 672, with sixteen 767); fewer
+// in small ones, which would leave most of the chip without a workgroup.
+constexpr int kBigThreads = 1024, kBigItems = 4;
+int tile_class(int64_t n) { return n <= 65536 ? 0 : (n <= (1 << 19) ? 1 : 2); }
+int tile_size(int64_t n) { return tile_class(n) == 0 ? 1024 : (tile_class(n) == 1 ? 2048 : kBigThreads * kBigItems); }
+
+// Digits of a key of `bits` bits: `part` leading bits (0: one bucket), `mid` low bits (0: no middle scatter), `last`.
+struct SortPlan {
+    int part, mid, last;
+};
+
+// One bucket while its digit counts stay small enough for the one workgroup that scans them (half a MB; 2 MB took it
+// 43 of 84 us); else half of the bits up to eight lead, and what remains is one digit of at most twelve bits or two.
+SortPlan sort_plan(int64_t n, int bits) {
+    const int64_t tiles = (n + tile_size(n) - 1) / tile_size(n);
+    if (bits <= kLastBits && tile_class(n) < 2 && (tiles << bits) <= (1 << 17)) return SortPlan{0, 0, bits};
+    const int most = tile_class(n) < 2 ? kLastBits : kLastBitsBig;
+    const int part = std::max(std::min(8, (bits + 1) / 2), bits - 2 * most), rest = bits - part;
+    if (rest <= most) return SortPlan{part, 0, rest};
+    return SortPlan{part, rest / 2, rest - rest / 2};
 }
 
-hipError_t radix_sort_pairs(int32_t *keys, int32_t *vals, int32_t *keys_tmp, int32_t *vals_tmp, void *temp,
-                            int64_t n, int key_bits, hipStream_t st, int32_t **keys_out, int32_t **vals_out) {
-    *keys_out = keys;
-    *vals_out = vals;
-    if (n <= 1 || key_bits <= 0) return hipSuccess;
-    int passes = (key_bits + kRadixMaxBits - 1) / kRadixMaxBits;
-    int bits = (key_bits + passes - 1) / passes;
-    int ntiles = (int)((n + kTile - 1) / kTile);
-    int64_t hist = (int64_t)ntiles << bits;
-    uint32_t *thist = (uint32_t *)temp;
-    uint32_t *toff = thist + (size_t)ntiles * kRadixBins;
-    char *scan_tmp = (char *)(((uintptr_t)(toff + (size_t)ntiles * kRadixBins) + 255) & ~(uintptr_t)255);
-    int32_t *ka = keys, *va = vals, *kb = keys_tmp, *vb = vals_tmp;
-    for (int p = 0, shift = 0; p < passes; p++, shift += bits) {
-        int pb = (key_bits - shift) < bits ? (key_bits - shift) : bits;
-        int64_t h = (int64_t)ntiles << pb;
-        (void)hist;
-        hipLaunchKernelGGL(k_radix_hist, dim3(ntiles), dim3(kTileThreads), 0, st, ka, n, shift, pb, thist, ntiles);
-        hipError_t e = hipGetLastError();
+// Most tiles of a call of at most n elements, buckets included.
+int64_t most_tiles(int64_t n) { return n / (kBigThreads * kBigItems) + 1 + 256 + kMaxBuckets; }
+
+size_t aligned(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+
+template <int THREADS, int ITEMS, int OUT>
+hipError_t scatter(const SegArgs &a, unsigned grid, hipStream_t st) {
+    const size_t D = (size_t)1 << a.bits;
+    const size_t stage = std::min(THREADS * ITEMS, kStageMost);
+    const size_t lds = 20 * stage + 4 * D + 4 * (THREADS / 64) + 2 * (THREADS / 64) * D;
+    auto k = k_seg_scatter<THREADS, ITEMS, OUT>;
+    if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        e = scan_impl<uint32_t, OpAdd>(thist, toff, h, false, 0u, scan_tmp, st);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_radix_scatter, dim3(ntiles), dim3(kTileThreads), 0, st, ka, va, kb, vb, n, shift, pb,
-                           toff, ntiles);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        int32_t *t;
-        t = ka; ka = kb; kb = t;
-        t = va; va = vb; vb = t;
     }
-    *keys_out = ka;
-    *vals_out = va;
-    return hipSuccess;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(THREADS), lds, st, a);
+    return hipGetLastError();
+}
+
+template <int THREADS, int ITEMS>
+hipError_t sort_impl(const SortArgs &a, const SortPlan &pl, int bits, int32_t **keys_out, bool *have_starts,
+                     hipStream_t st) {
+    constexpr int TILE = THREADS * ITEMS;
+    const int64_t n = a.n;
+    const int ntiles = (int)((n + TILE - 1) / TILE);
+    // scratch: buckets, first slots of the digits, digit counts of the tiles; the partition's counts, their sums
+    // and the scan's levels share the space of the latter
+    char *p = (char *)a.temp;
+    Buckets *bk = (Buckets *)p;
+    p += aligned(sizeof(Buckets));
+    uint32_t *dbase = (uint32_t *)p;
+    p += aligned(sizeof(uint32_t) << std::min(bits, kPartBits + kLastBits));
+    uint32_t *rows = (uint32_t *)p;
+    const int first = pl.part ? pl.part : pl.last;
+    hipLaunchKernelGGL((k_bin<THREADS, ITEMS>), dim3(ntiles), dim3(THREADS), sizeof(uint32_t) << first, st, a.pos, n,
+                       a.boxes, a.n_boxes, a.keys_a, pl.part ? bits - pl.part : 0, first, rows, pl.part ? 0 : 1, a.err);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    SegArgs s;
+    s.kin = a.keys_a;
+    s.pos = a.pos;
+    s.pay = a.pay;
+    s.rows = rows;
+    s.dbase = dbase;
+    s.bk = nullptr;
+    s.boxes = a.boxes;
+    s.n_boxes = a.n_boxes;
+    s.n = n;
+    s.shift = 0;
+    s.bits = pl.last;
+    s.vout = a.perm;
+    s.out = a.spos;
+    *have_starts = pl.mid == 0;
+    if (!pl.part) {
+        hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(kSegScanThreads), 0, st, rows, dbase, (const Buckets *)nullptr, n,
+                           ntiles, pl.last, a.cell_start, a.n_cells);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        s.kout = *keys_out = a.keys_b;
+        return scatter<THREADS, ITEMS, kSegLastPos>(s, ntiles, st);
+    }
+    const int nb = 1 << pl.part;
+    uint32_t *toff = rows + (size_t)nb * ntiles;
+    char *scan_tmp = (char *)(((uintptr_t)(toff + (size_t)nb * ntiles) + 255) & ~(uintptr_t)255);
+    e = scan_impl<uint32_t, OpAdd>(rows, toff, (int64_t)nb * ntiles, false, 0u, scan_tmp, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_buckets, dim3(1), dim3(kMaxBuckets), 0, st, toff, ntiles, nb, n, TILE, bk);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    SegArgs q = s;
+    q.rows = toff;
+    q.shift = bits - pl.part;
+    q.bits = pl.part;
+    q.kout = a.keys_b;
+    q.vout = nullptr;
+    q.out = pl.mid ? a.spos : a.pay;   // the coordinates end up in pay before the last scatter
+    if ((e = scatter<THREADS, ITEMS, kSegPart>(q, ntiles, st)) != hipSuccess) return e;
+    s.bk = bk;
+    const unsigned grid = (unsigned)(ntiles + nb);   // at least the tiles of all buckets
+    auto digit = [&](const int32_t *keys, int shift, int nbits, bool starts) {
+        hipLaunchKernelGGL((k_seg_hist<THREADS, ITEMS>), dim3(grid), dim3(THREADS), sizeof(uint32_t) << nbits, st, keys,
+                           n, bk, shift, nbits, rows);
+        hipError_t r = hipGetLastError();
+        if (r != hipSuccess) return r;
+        hipLaunchKernelGGL(k_seg_scan, dim3(nb), dim3(kSegScanThreads), 0, st, rows, dbase, bk, n, 0, nbits,
+                           starts ? a.cell_start : (int32_t *)nullptr, a.n_cells);
+        return hipGetLastError();
+    };
+    if (!pl.mid) {
+        s.kin = a.keys_b;
+        s.kout = *keys_out = a.keys_a;
+        if ((e = digit(a.keys_b, 0, pl.last, true)) != hipSuccess) return e;
+        return scatter<THREADS, ITEMS, kSegLast>(s, grid, st);
+    }
+    if ((e = digit(a.keys_b, 0, pl.mid, false)) != hipSuccess) return e;
+    SegArgs m = s;
+    m.kin = a.keys_b;
+    m.pay = a.spos;
+    m.bits = pl.mid;
+    m.kout = a.keys_a;
+    m.out = a.pay;
+    if ((e = scatter<THREADS, ITEMS, kSegMid>(m, grid, st)) != hipSuccess) return e;
+    if ((e = digit(a.keys_a, pl.mid, pl.last, false)) != hipSuccess) return e;
+    s.kin = a.keys_a;
+    s.shift = pl.mid;
+    s.kout = *keys_out = a.keys_b;
+    return scatter<THREADS, ITEMS, kSegLast>(s, grid, st);
+}
+
+}  // namespace
+
+// Enough for every call of at most n particles and n_cells cells.
+size_t sort_temp_bytes(int64_t n, int key_bits) {
+    const int64_t tiles = most_tiles(n);
+    const size_t rows = std::max((size_t)tiles << std::min(key_bits, kLastBitsBig),
+                                 (size_t)(256 + kMaxBuckets) << std::min(key_bits, kLastBits));
+    const int64_t part = tiles * kMaxBuckets;
+    return aligned(sizeof(Buckets)) + aligned(sizeof(uint32_t) << std::min(key_bits, kPartBits + kLastBits)) +
+           std::max(aligned(rows * sizeof(uint32_t)),
+                    2 * (size_t)part * sizeof(uint32_t) + scan_levels_bytes(part, sizeof(uint32_t)) + 1024);
+}
+
+hipError_t sort_by_cell(const SortArgs &a, int key_bits, int32_t **keys_out, bool *have_starts, hipStream_t st) {
+    *keys_out = a.keys_a;
+    *have_starts = false;
+    if (a.n <= 0) return hipSuccess;
+    const SortPlan pl = sort_plan(a.n, key_bits);
+    switch (tile_class(a.n)) {
+        case 0: return sort_impl<256, 4>(a, pl, key_bits, keys_out, have_starts, st);
+        case 1: return sort_impl<256, 8>(a, pl, key_bits, keys_out, have_starts, st);
+        default: return sort_impl<kBigThreads, kBigItems>(a, pl, key_bits, keys_out, have_starts, st);
+    }
 }
 
 hipError_t launch_cell_start(const int32_t *keys_sorted, int64_t n, int64_t n_cells, int32_t *endpos,
@@ -437,14 +751,6 @@ hipError_t launch_cell_start(const int32_t *keys_sorted, int64_t n, int64_t n_ce
         if (e != hipSuccess) return e;
     }
     return scan_i32_max_inclusive(endpos, cell_start + 1, n_cells, scan_temp, st);
-}
-
-hipError_t launch_gather(const float *pos, const int32_t *perm, const int32_t *keys_sorted, int64_t n,
-                         const BoxDev *boxes, int n_boxes, float4 *spos, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather, dim3(grid_for(n, 256)), dim3(256), 0, st, pos, perm, keys_sorted, n, boxes,
-                       n_boxes, spos);
-    return hipGetLastError();
 }
 
 }  // namespace anf

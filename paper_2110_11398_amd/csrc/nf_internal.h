@@ -186,18 +186,26 @@ int *device_error_word(int device);   // host accessor (allocates on first use)
 // Launch helpers (cells.hip)
 hipError_t launch_set_boxes(const abacus_nf_box *boxes, int n_boxes, const int32_t *cell_base,
                             BoxDev *dst, hipStream_t st);
-hipError_t launch_bin(const float *pos, int64_t n, const BoxDev *boxes, int n_boxes, int32_t *keys,
-                      int32_t *vals, int *err, hipStream_t st);
-size_t radix_temp_bytes(int64_t n);
-hipError_t radix_sort_pairs(int32_t *keys, int32_t *vals, int32_t *keys_tmp, int32_t *vals_tmp,
-                            void *temp, int64_t n, int key_bits, hipStream_t st, int32_t **keys_out,
-                            int32_t **vals_out);
+// Sort by cell: binning, stable sort, cell-relative layout.  The sorted keys are one of the two key
+// buffers; *have_starts: cell_start [n_cells + 1] was written too (else launch_cell_start derives it from the keys).
+struct SortArgs {
+    const float *pos;
+    int64_t n, n_cells;
+    const BoxDev *boxes;
+    int n_boxes;
+    int32_t *keys_a, *keys_b, *perm;              // [n] each
+    float4 *pay;                                  // [n] coordinates and input index before the last scatter
+    float4 *spos;                                 // [n]
+    int32_t *cell_start;
+    void *temp;                                   // sort_temp_bytes
+    int *err;
+};
+size_t sort_temp_bytes(int64_t n, int key_bits);
+hipError_t sort_by_cell(const SortArgs &a, int key_bits, int32_t **keys_out, bool *have_starts, hipStream_t st);
 size_t scan_temp_bytes(int64_t n);
 hipError_t scan_i32_max_inclusive(const int32_t *in, int32_t *out, int64_t n, void *temp, hipStream_t st);
 hipError_t launch_cell_start(const int32_t *keys_sorted, int64_t n, int64_t n_cells, int32_t *endpos,
                              int32_t *cell_start, void *scan_temp, hipStream_t st);
-hipError_t launch_gather(const float *pos, const int32_t *perm, const int32_t *keys_sorted, int64_t n,
-                         const BoxDev *boxes, int n_boxes, float4 *spos, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st);
 
 // Cell multipoles (multipoles.hip)

@@ -137,6 +137,28 @@ def test_build_cells_is_exact(nf, case):
     c.free()
 
 
+@pytest.mark.parametrize("n,K", [(1, 5), (1023, 8), (1025, 16), (4097, 5), (65536, 16), (65537, 16), (70001, 32),
+                                 (131073, 15), (524288, 16), (524289, 16), (524289, 27), (600001, 64), (600001, 101),
+                                 (5000, 162), (70001, 162), (600001, 162)])
+def test_build_cells_at_the_edges_of_the_sort_plan(nf, n, K):
+    """One bucket and one digit, a partition and one digit, and a middle digit (cell indices of 7 to 23 bits), at
+    the edges of the three tile sizes; a third of the particles in one cell, so that one bucket has most tiles."""
+    rng = np.random.default_rng(n + K)
+    pos = rng.random((n, 3))
+    pos[: n // 3] = (np.array([K // 2, 1, K - 1]) + 0.25 + 0.5 * rng.random((n // 3, 3))) / K
+    pos = pos[rng.permutation(n)].astype(np.float32)
+    boxes = [(n, 1.0, K)]
+    perm, start, spos, keys = expected_cells(pos, boxes)
+    c = nf.build_cells(torch.from_numpy(pos).cuda(), boxes, 2)
+    nf.sync()
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_PERM).cpu().numpy(), perm)
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_CELL_START).cpu().numpy(), start)
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_CELL_KEY).cpu().numpy(), keys)
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_SPOS).cpu().numpy(), spos)
+    c.free()
+
+
+
 # ---------------------------------------------------------------- forces vs oracle
 
 @pytest.fixture(scope="module")
