@@ -456,7 +456,7 @@ static int forces_impl(abacus_nf_cells h, const double *eps, abacus_nf_kind kind
     }
     a.grid = h->grid;
     mark(h, 1, false, st);
-    hipError_t e = launch_set_force_boxes(eps, gm, kde_b, kind, h->boxes.data(), h->n_boxes, h->d_fbox, st);
+    hipError_t e = launch_set_force_boxes(eps, gm, kde_b, kind, h->boxes.data(), h->n_boxes, h->d_fbox, a, st);
     if (e == hipSuccess) e = build_work_list(a, st);
     mark(h, 1, true, st);
     mark(h, 2, false, st);
@@ -758,7 +758,7 @@ int abacus_nf_interactions(abacus_nf_cells h, void *hip_stream, int64_t *out) {
     if (rc != ABACUS_NF_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     ForcesArgs a = make_args(h, ABACUS_NF_SPLINE, ABACUS_NF_SUM_FP32, nullptr, device_error_word(dev));
-    hipError_t e = launch_count_interactions(a, false, st);
+    hipError_t e = launch_count_interactions(a, st);
     if (e != hipSuccess) return hip_fail(e);
     std::vector<WorkBox> wb((size_t)h->n_boxes);
     if (hipMemcpyAsync(wb.data(), h->wb, wb.size() * sizeof(WorkBox), hipMemcpyDeviceToHost, st) != hipSuccess ||

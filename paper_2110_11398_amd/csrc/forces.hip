@@ -48,9 +48,33 @@ struct FBoxChunk {
     int first, count;
 };
 
-__global__ void k_set_fbox(FBoxChunk c, ForceBox *dst) {
-    int i = threadIdx.x;
+// Clears the work state and the totals of boxes [first, first + count) for a new work list.
+__device__ inline void clear_work(WorkState *ws, WorkBox *wb, int first, int count, int grid) {
+    const int t = threadIdx.x;
+    for (int i = t; i < count; i += blockDim.x) wb[first + i] = WorkBox{0, 0, 0, 0, 0, 0};
+    if (first != 0) return;
+    if (t == 0) {
+        ws->partial_slots = 0;
+        ws->n_items = 0;
+        ws->overflow = 0;
+    }
+    // the first slots of every queue belong to the waves that start on it
+    if (t < kQueues) ws->cursor[t][0] = grid > t ? (grid - t + kQueues - 1) / kQueues * kWaves : 0;
+    if (t < kNumClasses) {
+        ws->class_count[t] = 0;
+        ws->class_fill[t] = 0;
+    }
+}
+
+__global__ __launch_bounds__(64) void k_set_fbox(FBoxChunk c, ForceBox *dst, WorkState *ws, WorkBox *wb, int grid) {
+    static_assert(kNumClasses <= 64 && kFBoxChunk <= 64, "one lane each");
+    const int i = threadIdx.x;
     if (i < c.count) dst[c.first + i] = c.f[i];
+    clear_work(ws, wb, c.first, c.count, grid);
+}
+
+__global__ __launch_bounds__(64) void k_wl_clear(WorkState *ws, WorkBox *wb, int n_boxes) {
+    clear_work(ws, wb, 0, n_boxes, 0);
 }
 
 // ---------------------------------------------------------------- near-field columns
@@ -94,13 +118,16 @@ __device__ inline void column_segments(const int32_t *__restrict__ cs, int colba
 
 __device__ inline int wrap(int v, int K) { return v < 0 ? v + K : (v >= K ? v - K : v); }
 
-// Number of near-field sources of cell c.
-__device__ inline int cell_sources(const int32_t *__restrict__ cs, const BoxDev &B, int lin, int R) {
+// Number of near-field sources of a cell: the loads of all columns in flight at once.
+template <int R>
+__device__ inline int cell_sources(const int32_t *__restrict__ cs, const BoxDev &B, int lin) {
     const int K = B.K;
     const int cz = lin % K, cy = (lin / K) % K, cx = lin / (K * K);
     int total = 0;
+#pragma unroll
     for (int dx = -R; dx <= R; dx++) {
         const int ex = wrap(cx + dx, K);
+#pragma unroll
         for (int dy = -R; dy <= R; dy++) {
             const int ey = wrap(cy + dy, K);
             ColSeg o;
@@ -137,25 +164,6 @@ __device__ inline int cell_class(int n, int nsrc, int S, int max_lanes, int part
 
 // ---------------------------------------------------------------- work-list kernels
 
-__global__ __launch_bounds__(256) void k_wl_clear(WorkState *ws, WorkBox *wb, int n_boxes, int grid) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_boxes) wb[i] = WorkBox{0, 0, 0, 0, 0, 0};
-    if (blockIdx.x == 0) {
-        const int t = threadIdx.x;
-        if (t == 0) {
-            ws->partial_slots = 0;
-            ws->n_items = 0;
-            ws->overflow = 0;
-        }
-        // the first slots of every queue belong to the waves that start on it
-        if (t < kQueues) ws->cursor[t][0] = grid > t ? (grid - t + kQueues - 1) / kQueues * kWaves : 0;
-        if (t < kNumClasses) {
-            ws->class_count[t] = 0;
-            ws->class_fill[t] = 0;
-        }
-    }
-}
-
 __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     return v;
@@ -166,8 +174,9 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
 // clears the per-cell maxima of |a|^2 the force pass is about to record.  A workgroup walks its cells in
 // strides and adds its totals once: with one addition per wave the atomics on the one box of a large batch
 // dominated (late-time box of 4.2 million cells: 0.81 ms).
+template <int R>
 __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs, const BoxDev *__restrict__ boxes,
-                                                  int n_boxes, int64_t n_cells, int R, int S, int max_lanes,
+                                                  int n_boxes, int64_t n_cells, int S, int max_lanes,
                                                   int32_t *__restrict__ cell_nsrc,
                                                   unsigned long long *__restrict__ amax, WorkBox *__restrict__ wb) {
     __shared__ unsigned long long part[4][4];
@@ -192,7 +201,7 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
                 open = b;
             }
             const BoxDev B = boxes[b];
-            nsrc = cell_sources(cs, B, (int)(c - B.cell_base), R);
+            nsrc = cell_sources<R>(cs, B, (int)(c - B.cell_base));
             const int tiles = tile_count(n, S, max_lanes), L0 = tile_at(n, S, max_lanes, 0).L;
             const unsigned long long iters = (unsigned long long)((nsrc + L0 - 1) / L0);
             v[0] += (unsigned long long)n * (unsigned long long)nsrc;
@@ -307,7 +316,7 @@ __global__ __launch_bounds__(256) void k_wl_emit(const int32_t *__restrict__ cs,
                                                  const BoxDev *__restrict__ boxes, int n_boxes, int64_t n_cells,
                                                  int S, int max_lanes, WorkState *ws,
                                                  Item *__restrict__ items, int64_t item_capacity,
-                                                 int64_t partial_capacity, int *err) {
+                                                 int64_t partial_capacity, int per_block, int *err) {
     __shared__ int32_t cnt[kNumClasses];
     __shared__ int64_t cbase[kNumClasses];
     __shared__ int32_t over;
@@ -347,9 +356,9 @@ __global__ __launch_bounds__(256) void k_wl_emit(const int32_t *__restrict__ cs,
         }
     }
     __syncthreads();
-    const int64_t c0 = (int64_t)blockIdx.x * blockDim.x, c = c0 + threadIdx.x;
+    const int64_t c0 = (int64_t)blockIdx.x * per_block, c = c0 + threadIdx.x;
     int tiles = 0, parts = 0, cls = 0, local = 0, b = 0;
-    if (c < n_cells && !over) {
+    if ((int)threadIdx.x < per_block && c < n_cells && !over) {
         const int n = cs[c + 1] - cs[c];
         if (n > 0) {
             b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
@@ -946,12 +955,12 @@ __global__ __launch_bounds__(256) void k_finalize(const WorkState *__restrict__ 
                 double v;   // the value before its (optional) rounding to FP32
                 if constexpr (MODE == ABACUS_NF_SUM_FP32) {
                     float t = 0.f;
-#pragma unroll 4
+#pragma unroll 8
                     for (int p = 0; p < P; p++) t += (float)partials[NC * (base + (int64_t)p * nc) + d];
                     v = d < 3 ? t * F.scalef : t;
                 } else {
                     double t = 0.0;
-#pragma unroll 4
+#pragma unroll 8
                     for (int p = 0; p < P; p++) t += partials[NC * (base + (int64_t)p * nc) + d];
                     v = d < 3 ? t * F.scale : t;
                 }
@@ -1054,7 +1063,8 @@ size_t region_bytes(const abacus_nf_tuning &t) {
 // ---------------------------------------------------------------- host side
 
 hipError_t launch_set_force_boxes(const double *eps, const double *gm, const double *kde_b, abacus_nf_kind kind,
-                                  const abacus_nf_box *boxes, int n_boxes, ForceBox *dst, hipStream_t st) {
+                                  const abacus_nf_box *boxes, int n_boxes, ForceBox *dst, const ForcesArgs &a,
+                                  hipStream_t st) {
     for (int first = 0; first < n_boxes; first += kFBoxChunk) {
         FBoxChunk ch;
         memset(&ch, 0, sizeof(ch));
@@ -1083,28 +1093,35 @@ hipError_t launch_set_force_boxes(const double *eps, const double *gm, const dou
             }
             f.pad = 0;
         }
-        hipLaunchKernelGGL(k_set_fbox, dim3(1), dim3(kFBoxChunk), 0, st, ch, dst);
+        hipLaunchKernelGGL(k_set_fbox, dim3(1), dim3(64), 0, st, ch, dst, a.ws, a.wb, a.grid);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
     return hipSuccess;
 }
 
-hipError_t launch_count_interactions(const ForcesArgs &a, bool clear_amax, hipStream_t st) {
-    hipLaunchKernelGGL(k_wl_clear, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.n_boxes,
-                       a.grid);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || a.n_cells <= 0) return e;
+namespace {
+
+hipError_t launch_cells(const ForcesArgs &a, bool clear_amax, hipStream_t st) {
+    if (a.n_cells <= 0) return hipSuccess;
     // at most 2048 workgroups (eight per CU), so that their additions to a box's totals stay few
     const unsigned g = grid_for(a.n_cells, 256);
-    hipLaunchKernelGGL(k_wl_cells, dim3(g < 2048 ? g : 2048), dim3(256), 0, st, a.cell_start, a.boxes, a.n_boxes,
-                       a.n_cells, a.R, a.tune.sinks_per_lane, a.tune.max_lanes, a.cell_nsrc,
-                       clear_amax ? a.amax : nullptr, a.wb);
+    auto k = a.R == 1 ? k_wl_cells<1> : (a.R == 2 ? k_wl_cells<2> : k_wl_cells<3>);
+    hipLaunchKernelGGL(k, dim3(g < 2048 ? g : 2048), dim3(256), 0, st, a.cell_start, a.boxes, a.n_boxes, a.n_cells,
+                       a.tune.sinks_per_lane, a.tune.max_lanes, a.cell_nsrc, clear_amax ? a.amax : nullptr, a.wb);
     return hipGetLastError();
 }
 
+}  // namespace
+
+hipError_t launch_count_interactions(const ForcesArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL(k_wl_clear, dim3(1), dim3(64), 0, st, a.ws, a.wb, a.n_boxes);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_cells(a, false, st);
+}
+
 hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
-    hipError_t e = launch_count_interactions(a, true, st);
+    hipError_t e = launch_cells(a, true, st);
     if (e != hipSuccess || a.n_cells <= 0) return e;
     const int S = a.tune.sinks_per_lane, ML = a.tune.max_lanes;
     const unsigned gc = grid_for(a.n_cells, 256);
@@ -1114,8 +1131,11 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(k_wl_count, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
                        a.n_cells, S, ML, a.wb, a.ws, a.cell_parts, a.cell_pbase);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wl_emit, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.cell_parts, a.boxes,
-                       a.n_boxes, a.n_cells, S, ML, a.ws, a.items, a.item_capacity, a.partial_capacity, a.err);
+    // few cells have many items each: fewer cells to a workgroup then
+    const int per_block = a.n_cells >= 65536 ? 256 : 16;
+    hipLaunchKernelGGL(k_wl_emit, dim3(grid_for(a.n_cells, per_block)), dim3(256), 0, st, a.cell_start, a.cell_nsrc,
+                       a.cell_parts, a.boxes, a.n_boxes, a.n_cells, S, ML, a.ws, a.items, a.item_capacity,
+                       a.partial_capacity, per_block, a.err);
     return hipGetLastError();
 }
 

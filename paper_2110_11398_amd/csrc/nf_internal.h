@@ -255,14 +255,16 @@ struct ForcesArgs {
     int grid;        // persistent-kernel workgroups
 };
 
+// The per-box constants of a forces call; also clears the work state for build_work_list.
 hipError_t launch_set_force_boxes(const double *eps, const double *gm, const double *kde_b, abacus_nf_kind kind,
-                                  const abacus_nf_box *boxes, int n_boxes, ForceBox *dst, hipStream_t st);
+                                  const abacus_nf_box *boxes, int n_boxes, ForceBox *dst, const ForcesArgs &a,
+                                  hipStream_t st);
 hipError_t build_work_list(const ForcesArgs &a, hipStream_t st);
 hipError_t launch_forces(const ForcesArgs &a, hipStream_t st);
 hipError_t launch_finalize(const ForcesArgs &a, hipStream_t st);
 int forces_grid(const abacus_nf_tuning &t, abacus_nf_kind kind, abacus_nf_sum mode, bool kde, int device);
 // Fills wb[b].pairs of every box (and the totals the work list is planned from).
-hipError_t launch_count_interactions(const ForcesArgs &a, bool clear_amax, hipStream_t st);
+hipError_t launch_count_interactions(const ForcesArgs &a, hipStream_t st);
 
 // Leapfrog time stepping (kdk.hip)
 hipError_t upload_box_doubles(const double *host, int n_boxes, double *dev, hipStream_t st);
