@@ -433,6 +433,14 @@ struct ColOff {
     float x, y, czref;
 };
 
+// Second run of a column that wraps through the box boundary: its first slot in the flattened list, and what to add
+// to a flattened slot there to get the slot of the source.
+struct ColWrap {
+    int32_t split, base;
+};
+
+constexpr size_t kColBytes = 2 * kMaxCols * sizeof(ColOff) + kMaxCols * sizeof(ColWrap);
+
 // Orders LDS traffic between the lanes of one wave (no other wave takes part).
 __device__ inline void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -441,6 +449,9 @@ __device__ inline void wave_lds_sync() {
 }
 
 __device__ inline int sgpr(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// A wave-uniform float held in a scalar register.
+__device__ inline float uniform(float v) { return __builtin_bit_cast(float, sgpr(__builtin_bit_cast(int, v))); }
 
 // Knuth's two-sum: s + e == a + b exactly.
 __device__ __forceinline__ void two_sum(float a, float b, float &s, float &e) {
@@ -523,6 +534,9 @@ __device__ __forceinline__ void accumulate(const float4 (&p)[U], const float (&x
             // patterns of r^2 order as unsigned integers like the values: half a three-way integer minimum per
             // pair, one compare per group.
             if (__builtin_amdgcn_ballot_w64(rmin < __float_as_uint(e2))) {
+                // the constants stay in scalar registers outside this branch (copies hoisted into vector registers
+                // cost the main loop spills, whose reloads wait for the chunk being fetched)
+                asm volatile("" : "+s"(c0), "+s"(c1), "+s"(c2));
 #pragma unroll
                 for (int u = 0; u < G; u++)
 #pragma unroll
@@ -586,7 +600,8 @@ void k_forces(KArgs a) {
     float4 *stage = (float4 *)region;
     double *red = (double *)region;
     float *redf = (float *)region;
-    ColOff *coff = (ColOff *)(region + (size_t)a.region - 2 * kMaxCols * sizeof(ColOff));
+    ColOff *coff = (ColOff *)(region + (size_t)a.region - kColBytes);
+    ColWrap *cwrap = (ColWrap *)(coff + 2 * kMaxCols);
     const int R = a.R;
     const int W = 2 * R + 1;
     const int ncol = W * W;
@@ -656,7 +671,7 @@ void k_forces(KArgs a) {
         }
 
         // the near field, one column per lane, flattened by a prefix sum: source q of column `lane` is slot
-        // q + base0 (the first len0 of them) or q + base1
+        // q + base0, in its second run q + cwrap's base
         ColSeg o;
         o.src0 = o.len0 = o.src1 = o.len1 = 0;
         o.czref0 = o.czref1 = 0.f;
@@ -672,12 +687,13 @@ void k_forces(KArgs a) {
         }
         const int nsrc = sgpr(__shfl(incl, 63));
         const int cend = incl;                               // end of the column in the flattened list
-        const int csplit = incl - o.len1;                    // where its second run starts
-        const int base0 = o.src0 - (incl - (o.len0 + o.len1)), base1 = o.src1 - csplit;
+        const int base0 = o.src0 - (incl - (o.len0 + o.len1));
+        const unsigned long long wraps = __ballot(o.len1 > 0);   // columns of two runs
         if (lane < ncol) {
             const float ox = (float)(lane / W - R), oy = (float)(lane % W - R);
             coff[2 * lane] = ColOff{ox, oy, o.czref0};
             coff[2 * lane + 1] = ColOff{ox, oy, o.czref1};
+            cwrap[lane] = ColWrap{incl - o.len1, o.src1 - (incl - o.len1)};
         }
 
         const int P = a.cell_parts[c];
@@ -704,8 +720,8 @@ void k_forces(KArgs a) {
             rh[s] = 0.f;
             rhd[s] = 0.0;
         }
-        const float c0 = F.c0, c1 = F.c1, c2 = F.c2, e2 = F.eps2;
-        const float ib2 = F.kde_ib2, kc = F.kde_c;
+        const float c0 = uniform(F.c0), c1 = uniform(F.c1), c2 = uniform(F.c2), e2 = uniform(F.eps2);
+        const float ib2 = uniform(F.kde_ib2), kc = uniform(F.kde_c);
         const int step = L * U;
         const int nmax = (a.chunk / step) * step;
 
@@ -727,9 +743,9 @@ void k_forces(KArgs a) {
             for (;; ci++) {
                 const int e = __builtin_amdgcn_readlane(cend, ci);
                 if (e > f) {
-                    const int b0 = __builtin_amdgcn_readlane(base0, ci), m = __builtin_amdgcn_readlane(csplit, ci);
+                    const int b0 = __builtin_amdgcn_readlane(base0, ci);
                     const int b = e > stop ? stop : e;
-                    if (m == e) {   // one run
+                    if (!((wraps >> ci) & 1)) {   // one run
 #pragma unroll
                         for (int r = 0; r < kRounds; r++) {
                             const int q = f + 64 * r + lane;
@@ -739,7 +755,8 @@ void k_forces(KArgs a) {
                             }
                         }
                     } else {        // the column wraps through the box boundary
-                        const int b1 = __builtin_amdgcn_readlane(base1, ci);
+                        const ColWrap cw = cwrap[ci];
+                        const int m = cw.split, b1 = cw.base;
 #pragma unroll
                         for (int r = 0; r < kRounds; r++) {
                             const int q = f + 64 * r + lane;
@@ -758,8 +775,8 @@ void k_forces(KArgs a) {
             runs = (unsigned)w[0] | (unsigned)w[1] << 8 | (unsigned)w[2] << 16 | (unsigned)w[3] << 24;
         };
         if constexpr (kLowLds) store_low(low, lx, ly, lz);
+        wave_lds_sync();   // the column tables
         if (j0 < j1) fetch(j0, min(nmax, j1 - j0));
-        wave_lds_sync();   // coff, and the last item's reads of the region
 
         for (int f = j0; f < j1;) {
             const int n = min(nmax, j1 - f);
@@ -1055,7 +1072,7 @@ size_t region_bytes(const abacus_nf_tuning &t) {
     // the low words of the compensated sums at four sinks per lane lie behind a full chunk
     const size_t low = t.sinks_per_lane == 4 ? 64 * (kRounds * sizeof(float4) + 3 * sizeof(float4)) : 0;
     size_t main = std::max(std::max(stage, red), low);
-    return (main + 2 * kMaxCols * sizeof(ColOff) + 15) & ~(size_t)15;
+    return (main + kColBytes + 15) & ~(size_t)15;
 }
 
 }  // namespace
@@ -1132,7 +1149,7 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
                        a.n_cells, S, ML, a.wb, a.ws, a.cell_parts, a.cell_pbase);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // few cells have many items each: fewer cells to a workgroup then
-    const int per_block = a.n_cells >= 65536 ? 256 : 16;
+    const int per_block = a.n_cells >= 16384 ? 256 : 16;
     hipLaunchKernelGGL(k_wl_emit, dim3(grid_for(a.n_cells, per_block)), dim3(256), 0, st, a.cell_start, a.cell_nsrc,
                        a.cell_parts, a.boxes, a.n_boxes, a.n_cells, S, ML, a.ws, a.items, a.item_capacity,
                        a.partial_capacity, per_block, a.err);
