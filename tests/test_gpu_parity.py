@@ -246,6 +246,26 @@ def test_tile_cuts_of_cell_sizes(nf, cut_cells, tuning):
         c.free()
 
 
+@pytest.mark.parametrize("R", [1, 2, 3])
+@pytest.mark.parametrize("heavy", [1, 255, 257, 1025, 4099])
+def test_split_lists_of_small_boxes(nf, R, heavy):
+    """Boxes small enough that every source list is split to fill the chip, by default and with one or two sinks per
+    lane: a corner cell of `heavy` particles (sink tiles of every kind, partial sums of every part) in K = 2R + 1
+    cells, where each column of the near field wraps through the box boundary and runs end inside staged chunks."""
+    rng = np.random.default_rng(100 * R + heavy)
+    K = 2 * R + 1
+    corner = (np.array([0, K - 1, 0]) + rng.random((heavy, 3))) / K
+    pos = np.concatenate([rng.random((1500, 3)), corner])[rng.permutation(1500 + heavy)].astype(np.float32)
+    n, eps = len(pos), 0.02 / K
+    for kind in (SPLINE, PLUMMER):
+        ref, mag = oracle.forces(pos, 1.0, K, R, eps, kind, 1.0 / n, return_mag=True)
+        for mode, tuning in ((1, None), (0, None), (1, dict(sinks_per_lane=2, unroll=4)),
+                             (0, dict(sinks_per_lane=1, unroll=4, chunk=256))):
+            a, c = run(nf, pos, [(n, 1.0, K)], [eps], [1.0 / n], kind, mode, R, tuning)
+            check(a, ref, mag, f"R={R} heavy={heavy} kind={kind} mode={mode} {tuning}")
+            c.free()
+
+
 def _edge_case(case, rng):
     """(positions, [(n, L, K)], eps list, R)"""
     if case == "single":
