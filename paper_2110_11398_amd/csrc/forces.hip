@@ -171,9 +171,11 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
 
 // Per cell: source count; per box: exact pair total, unsplit items, and the sums that bound the partial slots
 // and items of a part length (slots <= n + slot_iters / length, items <= tiles + item_iters / length).  Also
-// clears the per-cell maxima of |a|^2 the force pass is about to record.  A workgroup walks its cells in
-// strides and adds its totals once: with one addition per wave the atomics on the one box of a large batch
-// dominated (late-time box of 4.2 million cells: 0.81 ms).
+// clears the per-cell maxima of |a|^2 the force pass is about to record.  Additions to one box's totals take
+// turns on their cache line and are kept few: with one box, workgroups walk the cells in strides and add once
+// (one addition per wave: 0.81 ms in a late-time box of 4.2 million cells); in a batch, every wave walks a run
+// of consecutive cells and adds when the box changes (strides, with each thread adding at every box it met,
+// took 25.8 ms for 64 boxes of 3.4 million cells in all; this takes 0.67 with the rest of the list).
 template <int R>
 __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs, const BoxDev *__restrict__ boxes,
                                                   int n_boxes, int64_t n_cells, int S, int max_lanes,
@@ -181,47 +183,66 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
                                                   unsigned long long *__restrict__ amax, WorkBox *__restrict__ wb) {
     __shared__ unsigned long long part[4][4];
     unsigned long long v[4] = {0, 0, 0, 0};   // pairs, slot_iters, item_iters, tiles of the open box
-    int open = -1;
-    auto flush = [&]() {   // this thread's totals alone (a box boundary inside the workgroup's cells)
-        if (open >= 0 && v[3]) {
-            atomicAdd(&wb[open].pairs, v[0]);
-            atomicAdd(&wb[open].slot_iters, v[1]);
-            atomicAdd(&wb[open].item_iters, v[2]);
-            atomicAdd(&wb[open].tiles, v[3]);
-        }
-        v[0] = v[1] = v[2] = v[3] = 0;
-    };
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += (int64_t)gridDim.x * blockDim.x) {
-        const int n = cs[c + 1] - cs[c];
+    // adds one cell's share to w and records its source count
+    auto count = [&](int64_t c, int n, int b, unsigned long long *w) {
         int nsrc = 0;
         if (n > 0) {
-            const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
-            if (b != open) {
-                flush();
-                open = b;
-            }
             const BoxDev B = boxes[b];
             nsrc = cell_sources<R>(cs, B, (int)(c - B.cell_base));
             const int tiles = tile_count(n, S, max_lanes), L0 = tile_at(n, S, max_lanes, 0).L;
             const unsigned long long iters = (unsigned long long)((nsrc + L0 - 1) / L0);
-            v[0] += (unsigned long long)n * (unsigned long long)nsrc;
-            v[1] += (unsigned long long)n * iters;
-            v[2] += (unsigned long long)tiles * iters;
-            v[3] += (unsigned long long)tiles;
+            w[0] += (unsigned long long)n * (unsigned long long)nsrc;
+            w[1] += (unsigned long long)n * iters;
+            w[2] += (unsigned long long)tiles * iters;
+            w[3] += (unsigned long long)tiles;
         }
         cell_nsrc[c] = nsrc;
         if (amax) amax[c] = 0;
-    }
-    if (n_boxes > 1) {   // one addition per wave whose lanes ended in one box
-        const int first = __builtin_amdgcn_readfirstlane(open);
-        if (first >= 0 && __ballot(open == first) == ~0ull) {
+    };
+    if (n_boxes > 1) {
+        const int lane = threadIdx.x & 63;
+        const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), waves = (int64_t)gridDim.x * 4;
+        const int64_t run = (n_cells + waves * 64 - 1) / (waves * 64) * 64;
+        const int64_t first = wave * run, end = first + run < n_cells ? first + run : n_cells;
+        int open = -1;
+        auto flush = [&]() {   // the whole wave
+            if (open < 0) return;
 #pragma unroll
             for (int q = 0; q < 4; q++) v[q] = wave_sum_u64(v[q]);
-            if ((threadIdx.x & 63) != 0) open = -1;
+            if (lane == 0) {
+                atomicAdd(&wb[open].pairs, v[0]);
+                atomicAdd(&wb[open].slot_iters, v[1]);
+                atomicAdd(&wb[open].item_iters, v[2]);
+                atomicAdd(&wb[open].tiles, v[3]);
+            }
+            v[0] = v[1] = v[2] = v[3] = 0;
+        };
+        for (int64_t c0 = first; c0 < end; c0 += 64) {
+            const int64_t c = c0 + lane;
+            unsigned long long w[4] = {0, 0, 0, 0};
+            int b = -1;   // stays so for an empty cell, which adds nothing
+            if (c < end) {
+                const int n = cs[c + 1] - cs[c];
+                if (n > 0) b = box_of_cell(boxes, n_boxes, (int32_t)c);
+                count(c, n, b, w);
+            }
+            for (unsigned long long left = __ballot(b >= 0); left;) {
+                const int x = __builtin_amdgcn_readlane(b, __ffsll((long long)left) - 1);
+                if (x != open) {
+                    flush();
+                    open = x;
+                }
+                if (b == x)
+#pragma unroll
+                    for (int q = 0; q < 4; q++) v[q] += w[q];
+                left &= ~__ballot(b == x);
+            }
         }
         flush();
         return;
     }
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += (int64_t)gridDim.x * blockDim.x)
+        count(c, cs[c + 1] - cs[c], 0, v);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         v[q] = wave_sum_u64(v[q]);
