@@ -266,6 +266,27 @@ def test_split_lists_of_small_boxes(nf, R, heavy):
             c.free()
 
 
+@pytest.mark.parametrize("Ks", [(3, 3, 4, 3, 5, 7), (5, 81, 3, 7), (90, 3, 4, 91)])
+def test_batches_count_their_cells_by_box(nf, Ks):
+    """Boxes that begin and end inside a wave's run of cells (one step of 64 cells; two with 524288 cells and more; runs
+    past the last cell), empty cells and an empty box among them: pairs counted and forces, against the boxes alone."""
+    rng = np.random.default_rng(sum(Ks))
+    counts = [0 if i == 2 else int(rng.integers(1, 3000)) for i in range(len(Ks))]
+    pos = [rng.random((n, 3)).astype(np.float32) for n in counts]
+    boxes, eps, gm = [(n, 1.0, K) for n, K in zip(counts, Ks)], [0.01] * len(Ks), [1.0] * len(Ks)
+    a, c = run(nf, np.concatenate(pos), boxes, eps, gm, SPLINE, 1, R=1)
+    pairs, at = 0, 0
+    for p, box in zip(pos, boxes):
+        if box[0]:
+            one, s = run(nf, p, [box], [0.01], [1.0], SPLINE, 1, R=1)
+            assert np.array_equal(a[at:at + box[0]], one), box
+            pairs += s.interactions()
+            s.free()
+        at += box[0]
+    assert c.interactions() == pairs
+    c.free()
+
+
 def _edge_case(case, rng):
     """(positions, [(n, L, K)], eps list, R)"""
     if case == "single":
