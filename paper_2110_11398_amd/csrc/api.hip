@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "nf_internal.h"
+#include "sort_plan.h"
 
 using namespace anf;
 

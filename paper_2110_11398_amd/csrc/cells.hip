@@ -29,6 +29,7 @@
 #include <cstring>
 
 #include "nf_internal.h"
+#include "sort_plan.h"
 
 namespace anf {
 
@@ -37,6 +38,7 @@ namespace {
 constexpr int kTileThreads = 256;
 constexpr int kTileItems = 16;
 constexpr int kTile = kTileThreads * kTileItems;  // elements per workgroup of a scan
+static_assert(kTile == kScanTile, "scratch of the scans");
 
 inline unsigned grid_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
@@ -172,16 +174,6 @@ __global__ void k_scan_add(T *out, const T *offs, int64_t n) {
     }
 }
 
-size_t scan_levels_bytes(int64_t n, size_t elem) {
-    size_t bytes = 0;
-    while (n > kTile) {
-        int64_t nt = (n + kTile - 1) / kTile;
-        bytes += 2 * (size_t)nt * elem + 256;
-        n = nt;
-    }
-    return bytes;
-}
-
 template <typename T, typename Op>
 hipError_t scan_impl(const T *in, T *out, int64_t n, bool inclusive, T identity, char *temp, hipStream_t st) {
     if (n <= 0) return hipSuccess;
@@ -205,18 +197,6 @@ hipError_t scan_impl(const T *in, T *out, int64_t n, bool inclusive, T identity,
 }
 
 // ---------------------------------------------------------------- sort by cell
-
-constexpr int kPartBits = 8;                 // most bits of the leading digit
-constexpr int kMaxBuckets = 1 << kPartBits;
-constexpr int kLastBits = 12;                 // most bits of a digit inside a bucket
-constexpr int kLastBitsBig = 11;              // the same in large calls (sixteen waves' counts in LDS)
-
-// Buckets of the partitioned order and the tiles they are cut into: bucket b is slots [start[b], start[b + 1]) and
-// tiles [tile[b], tile[b + 1]); an empty bucket has one (empty) tile.
-struct Buckets {
-    uint32_t start[kMaxBuckets + 1];
-    int32_t tile[kMaxBuckets + 1];
-};
 
 __global__ __launch_bounds__(kMaxBuckets) void k_buckets(const uint32_t *__restrict__ toff, int ntiles, int nb, int64_t n,
                                                          int tile, Buckets *__restrict__ o) {
@@ -584,34 +564,6 @@ hipError_t scan_i32_max_inclusive(const int32_t *in, int32_t *out, int64_t n, vo
 
 namespace {
 
-// Tiles: 4096 elements in large calls, four to a thread, so that two workgroups of sixteen waves fit a CU (build of
-// the clustered box of 16.7 million particles: 607 us; 512 threads with eight elements 672, with sixteen 767); fewer
-// in small ones, which would leave most of the chip without a workgroup.
-constexpr int kBigThreads = 1024, kBigItems = 4;
-int tile_class(int64_t n) { return n <= 65536 ? 0 : (n <= (1 << 19) ? 1 : 2); }
-int tile_size(int64_t n) { return tile_class(n) == 0 ? 1024 : (tile_class(n) == 1 ? 2048 : kBigThreads * kBigItems); }
-
-// Digits of a key of `bits` bits: `part` leading bits (0: one bucket), `mid` low bits (0: no middle scatter), `last`.
-struct SortPlan {
-    int part, mid, last;
-};
-
-// One bucket while its digit counts stay small enough for the one workgroup that scans them (half a MB; 2 MB took it
-// 43 of 84 us); else half of the bits up to eight lead, and what remains is one digit of at most twelve bits or two.
-SortPlan sort_plan(int64_t n, int bits) {
-    const int64_t tiles = (n + tile_size(n) - 1) / tile_size(n);
-    if (bits <= kLastBits && tile_class(n) < 2 && (tiles << bits) <= (1 << 17)) return SortPlan{0, 0, bits};
-    const int most = tile_class(n) < 2 ? kLastBits : kLastBitsBig;
-    const int part = std::max(std::min(8, (bits + 1) / 2), bits - 2 * most), rest = bits - part;
-    if (rest <= most) return SortPlan{part, 0, rest};
-    return SortPlan{part, rest / 2, rest - rest / 2};
-}
-
-// Most tiles of a call of at most n elements, buckets included.
-int64_t most_tiles(int64_t n) { return n / (kBigThreads * kBigItems) + 1 + 256 + kMaxBuckets; }
-
-size_t aligned(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
-
 template <int THREADS, int ITEMS, int OUT>
 hipError_t scatter(const SegArgs &a, unsigned grid, hipStream_t st) {
     const size_t D = (size_t)1 << a.bits;
@@ -632,14 +584,9 @@ hipError_t sort_impl(const SortArgs &a, const SortPlan &pl, int bits, int32_t **
     constexpr int TILE = THREADS * ITEMS;
     const int64_t n = a.n;
     const int ntiles = (int)((n + TILE - 1) / TILE);
-    // scratch: buckets, first slots of the digits, digit counts of the tiles; the partition's counts, their sums
-    // and the scan's levels share the space of the latter
-    char *p = (char *)a.temp;
-    Buckets *bk = (Buckets *)p;
-    p += aligned(sizeof(Buckets));
-    uint32_t *dbase = (uint32_t *)p;
-    p += aligned(sizeof(uint32_t) << std::min(bits, kPartBits + kLastBits));
-    uint32_t *rows = (uint32_t *)p;
+    const SortScratch at = sort_scratch(n, pl);
+    Buckets *bk = (Buckets *)a.temp;
+    uint32_t *dbase = (uint32_t *)((char *)a.temp + at.dbase), *rows = (uint32_t *)((char *)a.temp + at.rows);
     const int first = pl.part ? pl.part : pl.last;
     hipLaunchKernelGGL((k_bin<THREADS, ITEMS>), dim3(ntiles), dim3(THREADS), sizeof(uint32_t) << first, st, a.pos, n,
                        a.boxes, a.n_boxes, a.keys_a, pl.part ? bits - pl.part : 0, first, rows, pl.part ? 0 : 1, a.err);
@@ -715,17 +662,6 @@ hipError_t sort_impl(const SortArgs &a, const SortPlan &pl, int bits, int32_t **
 }
 
 }  // namespace
-
-// Enough for every call of at most n particles and n_cells cells.
-size_t sort_temp_bytes(int64_t n, int key_bits) {
-    const int64_t tiles = most_tiles(n);
-    const size_t rows = std::max((size_t)tiles << std::min(key_bits, kLastBitsBig),
-                                 (size_t)(256 + kMaxBuckets) << std::min(key_bits, kLastBits));
-    const int64_t part = tiles * kMaxBuckets;
-    return aligned(sizeof(Buckets)) + aligned(sizeof(uint32_t) << std::min(key_bits, kPartBits + kLastBits)) +
-           std::max(aligned(rows * sizeof(uint32_t)),
-                    2 * (size_t)part * sizeof(uint32_t) + scan_levels_bytes(part, sizeof(uint32_t)) + 1024);
-}
 
 hipError_t sort_by_cell(const SortArgs &a, int key_bits, int32_t **keys_out, bool *have_starts, hipStream_t st) {
     *keys_out = a.keys_a;

@@ -197,10 +197,9 @@ struct SortArgs {
     float4 *pay;                                  // [n] coordinates and input index before the last scatter
     float4 *spos;                                 // [n]
     int32_t *cell_start;
-    void *temp;                                   // sort_temp_bytes
+    void *temp;                                   // sort_temp_bytes of at least n and key_bits
     int *err;
 };
-size_t sort_temp_bytes(int64_t n, int key_bits);
 hipError_t sort_by_cell(const SortArgs &a, int key_bits, int32_t **keys_out, bool *have_starts, hipStream_t st);
 size_t scan_temp_bytes(int64_t n);
 hipError_t scan_i32_max_inclusive(const int32_t *in, int32_t *out, int64_t n, void *temp, hipStream_t st);

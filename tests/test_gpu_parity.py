@@ -159,6 +159,28 @@ def test_build_cells_at_the_edges_of_the_sort_plan(nf, n, K):
 
 
 
+def test_build_cells_with_more_than_2_to_the_30_cells(nf):
+    """The longest keys (31 bits) in a call of the largest tiles: nine leading bits and two digits more."""
+    K, n = 1025, 600001
+    rng = np.random.default_rng(K)
+    pos = torch.from_numpy(rng.random((n, 3)).astype(np.float32)).cuda()
+    t = pos.double() * float(K)
+    cell = t.floor().clamp_max(K - 1)
+    key, perm = torch.sort(((cell[:, 0] * K + cell[:, 1]) * K + cell[:, 2]).long(), stable=True)
+    c = nf.build_cells(pos, [(n, 1.0, K)], 2)
+    nf.sync()
+    assert torch.equal(c.copy(nf.abacus_nf.ARRAY_PERM).long(), perm)
+    assert torch.equal(c.copy(nf.abacus_nf.ARRAY_CELL_KEY).long(), key)
+    spos = c.copy(nf.abacus_nf.ARRAY_SPOS)
+    assert torch.equal(spos[:, :3], (t - (cell + 0.5)).float()[perm])
+    assert torch.equal(spos[:, 3], cell[perm, 2].float())
+    start = c.copy(nf.abacus_nf.ARRAY_CELL_START)
+    for lo in range(0, K ** 3 + 1, 1 << 27):
+        hi = min(K ** 3 + 1, lo + (1 << 27))
+        assert torch.equal(start[lo:hi].long(), torch.searchsorted(key, torch.arange(lo, hi, device="cuda"))), lo
+    c.free()
+
+
 # ---------------------------------------------------------------- forces vs oracle
 
 @pytest.fixture(scope="module")
