@@ -413,18 +413,14 @@ static int check_force_args(abacus_nf_cells h, const double *eps, abacus_nf_kind
 }
 
 static int ensure_work_buffers(abacus_nf_cells_s *h) {
-    const int64_t n = std::max<int64_t>(h->n_total, 1);
     const int64_t nc = std::max<int64_t>(h->n_cells, 1);
-    // unsplit items: one tile per non-empty cell, one per 64 sink groups, and at most one more per 11
-    // groups of a cell's rest (its binary cut); split source lists take the rest of the capacity
-    const int64_t want_items = h->tune.item_capacity > 0
-                                   ? h->tune.item_capacity
-                                   : std::min<int64_t>(INT32_MAX - 1, std::min(n, nc) + n / 16 + n / 11 + (1 << 16));
-    // split lists: a partial slot per sink and part; every box has room for the parts that fill the chip with it
-    // alone (64 lanes x 4 sinks x kFillItems items at most; parts of kMinPart iterations in small boxes)
-    int64_t want_partials = 2 * n + (1 << 16);
-    for (const abacus_nf_box &b : h->boxes)
-        want_partials += std::min<int64_t>(32 * b.n, (int64_t)(256 * kFillItems));
+    int64_t want_items = 0, want_partials = 0;
+    for (const abacus_nf_box &b : h->boxes) {
+        want_items += box_items(b.n, (int64_t)b.K * b.K * b.K);
+        want_partials += box_slots(b.n);
+    }
+    want_items = std::min<int64_t>(want_items, INT32_MAX - 1);
+    if (h->tune.item_capacity > 0) want_items = h->tune.item_capacity;
     if (h->wcap_cells >= nc && h->wcap_items == want_items && h->wcap_partials >= want_partials &&
         h->wcap_boxes >= h->n_boxes)
         return ABACUS_NF_OK;
@@ -472,6 +468,7 @@ static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf
     a.cell_pbase = h->cell_pbase;
     a.partials = h->partials;
     a.partial_capacity = h->wcap_partials;
+    a.shared_room = h->tune.item_capacity > 0;
     a.amax = h->cell_amax;
     a.acc = acc;
     a.rho = nullptr;

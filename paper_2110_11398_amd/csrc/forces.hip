@@ -256,49 +256,56 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
     }
 }
 
-// Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
-// at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
-// leaves the rest of the chip idle until it ends.  The length follows from the box's own work alone, so a box
-// gives bit-identical forces whatever batch it is in.  It is at most the tuning's part_sources and at least
-// kMinPart, and every length is scaled up alike where partial slots or items would not fit.
-__global__ __launch_bounds__(256) void k_wl_plan(const WorkState *__restrict__ ws, WorkBox *__restrict__ wb, int n_boxes, int S,
-                                                 int part_sources, int64_t partial_capacity, int64_t item_capacity,
-                                                 int64_t n_total) {
-    __shared__ unsigned long long sum[3];   // slot and item bounds at the unscaled lengths, unsplit items
-    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
-    __syncthreads();
-    auto length = [&](const WorkBox &w) {
-        const unsigned long long fill = w.pairs / ((unsigned long long)(64 * S) * kFillItems);
-        const long long lo = kMinPart < part_sources ? kMinPart : part_sources;
-        const long long it = fill > (unsigned long long)part_sources ? part_sources : (long long)fill;
-        return it < lo ? lo : it;
-    };
-    unsigned long long slots = 0, items = 0, tiles = 0;
-    for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
-        const WorkBox w = wb[b];
-        const unsigned long long it = (unsigned long long)length(w);
-        slots += w.slot_iters / it + 1;
-        items += w.item_iters / it + 1;
-        tiles += w.tiles;
-    }
-    if (tiles) {
-        atomicAdd(&sum[0], slots);
-        atomicAdd(&sum[1], items);
-        atomicAdd(&sum[2], tiles);
-    }
-    __syncthreads();
-    const double pbudget = (double)(partial_capacity - n_total), ibudget = (double)item_capacity - (double)sum[2];
+// Factor that brings `slots` and `items` (bounds at some part length, tiles included in neither) into their rooms.
+__device__ inline double plan_scale(double slots, double items, double slot_room, double item_room) {
     double f = 1.0;
-    if ((double)sum[0] > pbudget) f = pbudget >= 1.0 ? (double)sum[0] / pbudget : 1e18;
-    if ((double)sum[1] > ibudget) {
-        const double fi = ibudget >= 1.0 ? (double)sum[1] / ibudget : 1e18;
+    if (slots > slot_room) f = slot_room >= 1.0 ? slots / slot_room : 1e18;
+    if (items > item_room) {
+        const double fi = item_room >= 1.0 ? items / item_room : 1e18;
         f = fi > f ? fi : f;
     }
-    if (f > 1.0) f *= 1.0 + 1e-9;
+    return f > 1.0 ? f * (1.0 + 1e-9) : 1.0;
+}
+
+// Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
+// at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
+// leaves the rest of the chip idle until it ends.  The length is at most the tuning's part_sources and at least
+// kMinPart, and longer where the box's own room (box_slots, box_items) is less than its parts would take: it
+// follows from the box alone, so a box gives bit-identical forces whatever batch it is in.  Only where the lists were
+// given less than the sum of these rooms are all lengths scaled up alike.
+__global__ __launch_bounds__(256) void k_wl_plan(WorkBox *__restrict__ wb, const BoxDev *__restrict__ boxes, int n_boxes,
+                                                 int S, int part_sources, int shared_room, int64_t partial_capacity,
+                                                 int64_t item_capacity, int64_t n_total) {
+    __shared__ unsigned long long sum[3];   // slot and item bounds at the boxes' own lengths, unsplit items
+    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
+    __syncthreads();
+    auto scaled = [](long long it, double f) {
+        const double v = f > 1.0 ? ceil((double)it * f) : (double)it;
+        return v > (double)INT_MAX ? INT_MAX : (int32_t)v;
+    };
     for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
-        const double it = f > 1.0 ? ceil((double)length(wb[b]) * f) : (double)length(wb[b]);
-        wb[b].part_iters = it > (double)INT_MAX ? INT_MAX : (int32_t)it;
+        const WorkBox w = wb[b];
+        const int64_t n = boxes[b].n, K = boxes[b].K;
+        const unsigned long long fill = w.pairs / ((unsigned long long)(64 * S) * kFillItems);
+        const long long lo = kMinPart < part_sources ? kMinPart : part_sources;
+        const long long want = fill > (unsigned long long)part_sources ? part_sources : (long long)fill;
+        const long long it = want < lo ? lo : want;
+        const double f = plan_scale((double)(w.slot_iters / it + 1), (double)(w.item_iters / it + 1),
+                                    (double)(box_slots(n) - n), (double)box_items(n, K * K * K) - (double)w.tiles);
+        const int32_t own = scaled(it, f);
+        wb[b].part_iters = own;
+        if (shared_room && w.tiles) {
+            atomicAdd(&sum[0], w.slot_iters / own + 1);
+            atomicAdd(&sum[1], w.item_iters / own + 1);
+            atomicAdd(&sum[2], w.tiles);
+        }
     }
+    if (!shared_room) return;
+    __syncthreads();
+    const double f = plan_scale((double)sum[0], (double)sum[1], (double)(partial_capacity - n_total),
+                                (double)item_capacity - (double)sum[2]);
+    if (f > 1.0)
+        for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) wb[b].part_iters = scaled(wb[b].part_iters, f);
 }
 
 __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
@@ -1163,8 +1170,8 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
     if (e != hipSuccess || a.n_cells <= 0) return e;
     const int S = a.tune.sinks_per_lane, ML = a.tune.max_lanes;
     const unsigned gc = grid_for(a.n_cells, 256);
-    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(256), 0, st, a.ws, a.wb, a.n_boxes, S, a.tune.part_sources,
-                       a.partial_capacity, a.item_capacity, a.n_total);
+    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(256), 0, st, a.wb, a.boxes, a.n_boxes, S,
+                       a.tune.part_sources, (int)a.shared_room, a.partial_capacity, a.item_capacity, a.n_total);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_wl_count, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
                        a.n_cells, S, ML, a.wb, a.ws, a.cell_parts, a.cell_pbase);

@@ -59,6 +59,19 @@ constexpr int kLightClaim = 4;
 constexpr unsigned long long kFillItems = 16384;
 constexpr long long kMinPart = 256;
 
+// Room of one box in the lists: the parts of its split source lists are made longer until they fit, so that a box is
+// cut in the same way whatever batch it is in.  Partial slots, one per sink and part: the parts that fill the chip
+// with the box alone are 64 lanes x 4 sinks x kFillItems slots at most, those of kMinPart iterations in small boxes
+// fewer.  Items: unsplit, one tile per non-empty cell, one per 64 sink groups and at most one more per 11 groups of a
+// cell's rest (its binary cut); split lists take the rest.
+__host__ __device__ inline int64_t box_slots(int64_t n) {
+    const int64_t a = 32 * n, b = 256 * (int64_t)kFillItems;
+    return 2 * n + (a < 65536 ? a : 65536) + (a < b ? a : b);
+}
+__host__ __device__ inline int64_t box_items(int64_t n, int64_t n_cells) {
+    return (n < n_cells ? n : n_cells) + n / 16 + n / 11 + (32 * n < 65536 ? 32 * n : 65536);
+}
+
 // Work of one box in a forces call.
 struct WorkBox {
     unsigned long long pairs;       // sum over cells of n_c * sources(c)
@@ -243,6 +256,7 @@ struct ForcesArgs {
     int64_t *cell_pbase;   // first partial slot of a split cell (unset for others)
     double *partials;
     int64_t partial_capacity;
+    bool shared_room;      // the lists hold less than the boxes' own rooms: all parts are made longer alike
     float *acc;
     double *acc64;   // FP64 accelerations instead of acc (nullptr: FP32 output)
     float *rho;      // density output (nullptr: forces only)

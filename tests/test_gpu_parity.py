@@ -434,6 +434,54 @@ def test_batched_boxes_equal_single_boxes(nf):
         off += b.n
 
 
+@pytest.mark.parametrize("form", ["fp32", "comp32", "fp64", "f64 output", "density"])
+def test_batched_boxes_equal_single_boxes_where_parts_fill_their_room(nf, form):
+    """Dense boxes whose split source lists would take more slots and items than they have room for, and sparse ones
+    with room to spare, in one batch: every box as if it were alone, and the dense ones as the oracle has them."""
+    rng = np.random.default_rng(11)
+    sizes = [(32768, 5), (150001, 40), (20011, 5), (0, 6), (700, 9), (24000, 5)]
+    pos = [rng.random((n, 3)).astype(np.float32) for n, K in sizes]
+    eps, gm, bs = [0.004] * 6, [1.0 / 4096] * 6, [0.01] * 6
+    mode = {"fp32": 0, "fp64": 2}.get(form, 1)
+
+    def call(pos, k):
+        """[(accelerations, densities or None)] of the boxes k in one batch, and the handle's maxima per cell"""
+        c = nf.build_cells(torch.from_numpy(np.concatenate([pos[i] for i in k])).cuda(),
+                           [(len(pos[i]), 1.0, sizes[i][1]) for i in k], 2)
+        e, g, b = ([v[i] for i in k] for v in (eps, gm, bs))
+        rho = None
+        if form == "density":
+            acc, rho = c.forces_density(e, g, b, SPLINE, mode)
+        elif form == "f64 output":
+            acc = c.forces_f64(e, g, SPLINE, mode)
+        else:
+            acc = c.forces(e, g, SPLINE, mode)
+        nf.sync()
+        amax = c.copy(nf.ARRAY_CELL_AMAX2).cpu().numpy()
+        c.free()
+        cut = np.cumsum([len(pos[i]) for i in k])[:-1]
+        parts = lambda t: np.split(t.cpu().numpy(), cut)
+        return parts(acc), parts(rho) if rho is not None else [None] * len(k), amax
+
+    accs, rhos, amax = call(pos, range(len(sizes)))
+    at = 0
+    for i, (n, K) in enumerate(sizes):
+        if n:
+            (a,), (r,), m = call(pos, [i])
+            assert np.array_equal(accs[i], a), (form, n)
+            assert r is None or np.array_equal(rhos[i], r), (form, n)
+            assert np.array_equal(amax[at:at + K ** 3], m), (form, n)
+            if i == 2:
+                ref, mag = oracle.forces(pos[i], 1.0, K, 2, eps[i], SPLINE, gm[i], return_mag=True)
+                check(a.astype(np.float64), ref, mag, f"dense box {form}")
+                cell = oracle.bin_cells(pos[i], 1.0, K)
+                a2 = (a.astype(np.float64) ** 2).sum(axis=1)
+                assert np.array_equal(m, [a2[cell == c].max() for c in range(K ** 3)])
+                if r is not None:
+                    check_density(r.astype(np.float64), oracle.density(pos[i], 1.0, K, 2, bs[i]), "dense box")
+        at += K ** 3
+
+
 def test_run_to_run_bit_identical(nf):
     w = gen.workload("clustered", side=64, K=16, n_halos=64)
     b = w.boxes[0]
