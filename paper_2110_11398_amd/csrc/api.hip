@@ -53,6 +53,7 @@ struct abacus_nf_cells_s {
 
     // force work buffers
     int64_t wcap_cells = -1, wcap_items = -1, wcap_partials = -1, wcap_boxes = -1;
+    int64_t want_slots = -1, want_items = -1;   // what the lists were sized for (they hold less where memory is short)
     ForceBox *d_fbox = nullptr;
     WorkState *ws = nullptr;
     WorkBox *wb = nullptr;
@@ -198,6 +199,7 @@ void free_work_buffers(abacus_nf_cells_s *h) {
     h->cell_amax = nullptr;
     h->amax_valid = false;
     h->wcap_cells = h->wcap_items = h->wcap_partials = h->wcap_boxes = -1;
+    h->want_slots = h->want_items = -1;
 }
 
 int key_bits(int64_t n_cells) {
@@ -413,37 +415,36 @@ static int check_force_args(abacus_nf_cells h, const double *eps, abacus_nf_kind
 }
 
 static int ensure_work_buffers(abacus_nf_cells_s *h) {
-    const int64_t nc = std::max<int64_t>(h->n_cells, 1);
-    int64_t want_items = 0, want_partials = 0;
-    for (const abacus_nf_box &b : h->boxes) {
-        want_items += box_items(b.n, (int64_t)b.K * b.K * b.K);
-        want_partials += box_slots(b.n);
-    }
-    want_items = std::min<int64_t>(want_items, INT32_MAX - 1);
-    if (h->tune.item_capacity > 0) want_items = h->tune.item_capacity;
-    if (h->wcap_cells >= nc && h->wcap_items == want_items && h->wcap_partials >= want_partials &&
-        h->wcap_boxes >= h->n_boxes)
+    const int64_t n = std::max<int64_t>(h->n_total, 1), nc = std::max<int64_t>(h->n_cells, 1);
+    const ListRoom want = list_room(n, nc, h->n_boxes);
+    const int64_t forced = h->tune.item_capacity, want_items = forced > 0 ? forced : want.items;
+    if (h->wcap_cells >= nc && h->wcap_boxes >= h->n_boxes && h->want_slots >= want.slots && h->want_items == want_items)
         return ABACUS_NF_OK;
-    free_work_buffers(h);
-    Carver m;
-    m.add(h->d_fbox, h->n_boxes);
-    m.add(h->ws, 1);
-    m.add(h->wb, h->n_boxes);
-    m.add(h->items, want_items);
-    m.add(h->cell_nsrc, nc);
-    m.add(h->cell_parts, nc);
-    m.add(h->cell_pbase, nc);
-    m.add(h->partials, 4 * want_partials);
-    m.add(h->cell_amax, nc);
-    if (!m.alloc(h->work_block)) {
+    for (const ListRoom &r : {want, least_room(n, nc)}) {   // the least lists where memory is short
         free_work_buffers(h);
-        return ABACUS_NF_ENOMEM;
+        const int64_t items = forced > 0 ? forced : r.items;
+        Carver m;
+        m.add(h->d_fbox, h->n_boxes);
+        m.add(h->ws, 1);
+        m.add(h->wb, h->n_boxes);
+        m.add(h->items, items);
+        m.add(h->cell_nsrc, nc);
+        m.add(h->cell_parts, nc);
+        m.add(h->cell_pbase, nc);
+        m.add(h->partials, 4 * r.slots);
+        m.add(h->cell_amax, nc);
+        if (m.alloc(h->work_block)) {
+            h->wcap_cells = nc;
+            h->wcap_items = items;
+            h->wcap_partials = r.slots;
+            h->wcap_boxes = h->n_boxes;
+            h->want_slots = want.slots;
+            h->want_items = want_items;
+            return ABACUS_NF_OK;
+        }
     }
-    h->wcap_cells = nc;
-    h->wcap_items = want_items;
-    h->wcap_partials = want_partials;
-    h->wcap_boxes = h->n_boxes;
-    return ABACUS_NF_OK;
+    free_work_buffers(h);
+    return ABACUS_NF_ENOMEM;
 }
 
 static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf_sum mode, float *acc, int *err) {
@@ -468,7 +469,12 @@ static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf
     a.cell_pbase = h->cell_pbase;
     a.partials = h->partials;
     a.partial_capacity = h->wcap_partials;
-    a.shared_room = h->tune.item_capacity > 0;
+    int64_t slots = 0, items = 0;
+    for (const abacus_nf_box &b : h->boxes) {
+        slots += box_slots(b.n);
+        items += box_items(b.n, (int64_t)b.K * b.K * b.K);
+    }
+    a.short_room = slots > a.partial_capacity || items > a.item_capacity;
     a.amax = h->cell_amax;
     a.acc = acc;
     a.rho = nullptr;

@@ -57,12 +57,15 @@ __device__ inline void clear_work(WorkState *ws, WorkBox *wb, int first, int cou
         ws->partial_slots = 0;
         ws->n_items = 0;
         ws->overflow = 0;
+        ws->whole_slots = ws->whole_items = 0;
     }
     // the first slots of every queue belong to the waves that start on it
     if (t < kQueues) ws->cursor[t][0] = grid > t ? (grid - t + kQueues - 1) / kQueues * kWaves : 0;
     if (t < kNumClasses) {
         ws->class_count[t] = 0;
         ws->class_fill[t] = 0;
+        ws->bin_slots[t] = 0;
+        ws->bin_items[t] = 0;
     }
 }
 
@@ -256,56 +259,103 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
     }
 }
 
-// Factor that brings `slots` and `items` (bounds at some part length, tiles included in neither) into their rooms.
-__device__ inline double plan_scale(double slots, double items, double slot_room, double item_room) {
-    double f = 1.0;
-    if (slots > slot_room) f = slot_room >= 1.0 ? slots / slot_room : 1e18;
-    if (items > item_room) {
-        const double fi = item_room >= 1.0 ? items / item_room : 1e18;
-        f = fi > f ? fi : f;
-    }
-    return f > 1.0 ? f * (1.0 + 1e-9) : 1.0;
-}
-
 // Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
 // at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
 // leaves the rest of the chip idle until it ends.  The length is at most the tuning's part_sources and at least
 // kMinPart, and longer where the box's own room (box_slots, box_items) is less than its parts would take: it
-// follows from the box alone, so a box gives bit-identical forces whatever batch it is in.  Only where the lists were
-// given less than the sum of these rooms are all lengths scaled up alike.
-__global__ __launch_bounds__(256) void k_wl_plan(WorkBox *__restrict__ wb, const BoxDev *__restrict__ boxes, int n_boxes,
-                                                 int S, int part_sources, int shared_room, int64_t partial_capacity,
-                                                 int64_t item_capacity, int64_t n_total) {
-    __shared__ unsigned long long sum[3];   // slot and item bounds at the boxes' own lengths, unsplit items
-    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
+// follows from the box alone, so a box gives bit-identical forces whatever batch it is in.
+//
+// What a batch decides is which cells are split over items at all.  A cell whose list is no longer than a wave's share
+// of the whole batch stays one item per tile, which goes through the parts in order and adds them up as k_finalize
+// would: no slots to write and read again (512 boxes of 32768 uniform particles: 41.6 ms with every cell split over
+// items, 40.8 with whole ones, the same bits).
+__global__ __launch_bounds__(256) void k_wl_plan(WorkState *__restrict__ ws, WorkBox *__restrict__ wb,
+                                                 const BoxDev *__restrict__ boxes, int n_boxes, int S,
+                                                 int part_sources) {
+    __shared__ unsigned long long pairs;
+    if (threadIdx.x == 0) pairs = 0;
     __syncthreads();
-    auto scaled = [](long long it, double f) {
-        const double v = f > 1.0 ? ceil((double)it * f) : (double)it;
-        return v > (double)INT_MAX ? INT_MAX : (int32_t)v;
-    };
+    const unsigned long long share = (unsigned long long)(64 * S) * kFillItems;
+    auto capped = [&](unsigned long long fill) { return fill > (unsigned long long)part_sources ? part_sources : (long long)fill; };
     for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
         const WorkBox w = wb[b];
         const int64_t n = boxes[b].n, K = boxes[b].K;
-        const unsigned long long fill = w.pairs / ((unsigned long long)(64 * S) * kFillItems);
-        const long long lo = kMinPart < part_sources ? kMinPart : part_sources;
-        const long long want = fill > (unsigned long long)part_sources ? part_sources : (long long)fill;
-        const long long it = want < lo ? lo : want;
-        const double f = plan_scale((double)(w.slot_iters / it + 1), (double)(w.item_iters / it + 1),
-                                    (double)(box_slots(n) - n), (double)box_items(n, K * K * K) - (double)w.tiles);
-        const int32_t own = scaled(it, f);
-        wb[b].part_iters = own;
-        if (shared_room && w.tiles) {
-            atomicAdd(&sum[0], w.slot_iters / own + 1);
-            atomicAdd(&sum[1], w.item_iters / own + 1);
-            atomicAdd(&sum[2], w.tiles);
+        const long long want = capped(w.pairs / share), it = want < kMinPart ? kMinPart : want;
+        // bounds at this length: slots <= n + slot_iters / length, items <= tiles + item_iters / length
+        const double slots = (double)(w.slot_iters / it + 1), items = (double)(w.item_iters / it + 1);
+        const double slot_room = (double)(box_slots(n) - n), item_room = (double)box_items(n, K * K * K) - (double)w.tiles;
+        double f = 1.0;
+        if (slots > slot_room) f = slot_room >= 1.0 ? slots / slot_room : 1e18;
+        if (items > item_room) f = fmax(f, item_room >= 1.0 ? items / item_room : 1e18);
+        const double v = f > 1.0 ? ceil((double)it * (f * (1.0 + 1e-9))) : (double)it;
+        wb[b].part_iters = v > (double)INT_MAX ? INT_MAX : (int32_t)v;
+        if (w.pairs) atomicAdd(&pairs, w.pairs);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        ws->whole_iters = (int32_t)capped(pairs / share);
+        ws->whole_bin = -1;
+    }
+}
+
+// Length bin of a cell's source list: half octaves of its source iterations.
+__device__ inline int length_bin(int iters) {
+    const int b = (int)(2.0f * log2f((float)iters));
+    return b < 0 ? 0 : (b >= kNumClasses ? kNumClasses - 1 : b);
+}
+
+// Parts of a cell, negative where they stay together in one item per tile.
+__device__ inline int cell_split(int n, int nsrc, int S, int max_lanes, int part_iters, int whole_iters, int whole_bin) {
+    const int parts = cell_part_count(n, nsrc, S, max_lanes, part_iters);
+    if (parts <= 1) return parts;
+    const int L0 = tile_at(n, S, max_lanes, 0).L, iters = (nsrc + L0 - 1) / L0;
+    return iters <= whole_iters || length_bin(iters) <= whole_bin ? -parts : parts;
+}
+
+// Where the boxes' rooms add up to more than the lists hold: what splitting the cells of every length bin takes.
+__global__ __launch_bounds__(256) void k_wl_bins(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
+                                                 const BoxDev *__restrict__ boxes, int n_boxes, int64_t n_cells, int S,
+                                                 int max_lanes, const WorkBox *__restrict__ wb, WorkState *ws) {
+    __shared__ unsigned long long slots[kNumClasses + 1], items[kNumClasses + 1];   // the last: with every cell whole
+    if (threadIdx.x <= kNumClasses) slots[threadIdx.x] = items[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int n = c < n_cells ? cs[c + 1] - cs[c] : 0;
+    if (n > 0) {
+        const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
+        const int nsrc = cell_nsrc[c], parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, ws->whole_iters, -1);
+        const unsigned long long tiles = (unsigned long long)tile_count(n, S, max_lanes);
+        atomicAdd(&items[kNumClasses], tiles);
+        if (parts < 0 || parts > 1) atomicAdd(&slots[kNumClasses], (unsigned long long)n);
+        if (parts > 1) {
+            const int L0 = tile_at(n, S, max_lanes, 0).L, bin = length_bin((nsrc + L0 - 1) / L0);
+            atomicAdd(&slots[bin], (unsigned long long)n * (unsigned long long)(parts - 1));
+            atomicAdd(&items[bin], tiles * (unsigned long long)(parts - 1));
         }
     }
-    if (!shared_room) return;
     __syncthreads();
-    const double f = plan_scale((double)sum[0], (double)sum[1], (double)(partial_capacity - n_total),
-                                (double)item_capacity - (double)sum[2]);
-    if (f > 1.0)
-        for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) wb[b].part_iters = scaled(wb[b].part_iters, f);
+    if (threadIdx.x <= kNumClasses) {
+        const int k = threadIdx.x;
+        if (slots[k]) atomicAdd(k < kNumClasses ? &ws->bin_slots[k] : &ws->whole_slots, slots[k]);
+        if (items[k]) atomicAdd(k < kNumClasses ? &ws->bin_items[k] : &ws->whole_items, items[k]);
+    }
+}
+
+// The shortest lists stay whole, bin by bin, until the others fit: one lane per bin.
+__global__ __launch_bounds__(64) void k_wl_fit(WorkState *ws, int64_t partial_capacity, int64_t item_capacity) {
+    static_assert(kNumClasses == 64, "one lane per bin");
+    const int k = threadIdx.x;
+    unsigned long long slots = ws->bin_slots[k], items = ws->bin_items[k];   // then of bins k and up
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long s = __shfl_down(slots, off), i = __shfl_down(items, off);
+        if (k + off < 64) {
+            slots += s;
+            items += i;
+        }
+    }
+    const unsigned long long too_many = __ballot(ws->whole_slots + slots > (unsigned long long)partial_capacity ||
+                                                 ws->whole_items + items > (unsigned long long)item_capacity);
+    if (k == 0) ws->whole_bin = 63 - __clzll((long long)too_many);   // -1: all fit
 }
 
 __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
@@ -324,17 +374,18 @@ __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs
         const int n = cs[c + 1] - cs[c];
         const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
         const int nsrc = cell_nsrc[c];
-        parts = cell_part_count(n, nsrc, S, max_lanes, wb[b].part_iters);
+        parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, ws->whole_iters, ws->whole_bin);
         cell_parts[c] = parts;
-        if (parts > 1) local = atomicAdd(&need, (unsigned long long)parts * (unsigned long long)n);
+        const int split = parts < 0 ? 1 : parts;
+        if (parts < 0 || parts > 1) local = atomicAdd(&need, (unsigned long long)split * (unsigned long long)n);
         if (n > 0)
-            atomicAdd(&hist[cell_class(n, nsrc, S, max_lanes, parts)], tile_count(n, S, max_lanes) * parts);
+            atomicAdd(&hist[cell_class(n, nsrc, S, max_lanes, split)], tile_count(n, S, max_lanes) * split);
     }
     __syncthreads();
     if (threadIdx.x == 0) base = need ? atomicAdd(&ws->partial_slots, need) : 0;
     if (threadIdx.x < kNumClasses && hist[threadIdx.x]) atomicAdd(&ws->class_count[threadIdx.x], hist[threadIdx.x]);
     __syncthreads();
-    if (parts > 1) cell_pbase[c] = (int64_t)(base + local);
+    if (parts < 0 || parts > 1) cell_pbase[c] = (int64_t)(base + local);
 }
 
 // Items in class order.  Every workgroup forms the class offsets (heaviest class first) from the counts; the
@@ -390,7 +441,7 @@ __global__ __launch_bounds__(256) void k_wl_emit(const int32_t *__restrict__ cs,
         const int n = cs[c + 1] - cs[c];
         if (n > 0) {
             b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
-            parts = cell_parts[c];
+            parts = cell_parts[c] < 0 ? 1 : cell_parts[c];
             tiles = tile_count(n, S, max_lanes);
             cls = cell_class(n, cell_nsrc[c], S, max_lanes, parts);
             local = atomicAdd(&cnt[cls], tiles * parts);
@@ -642,9 +693,10 @@ void k_forces(KArgs a) {
     // (32768 particles: 0.48 ms of 0.91).
     int x = blockIdx.x % kQueues;
     int jnext = (int)(blockIdx.x / kQueues) * kWaves + wave, jleft = 1;
+    int k = n_items, part = 0, parts_left = 0;   // parts of the last item that are still to be done
     for (;;) {
-        int k = n_items;
-        for (;;) {
+        if (parts_left == 0) k = n_items;
+        while (parts_left == 0) {
             if (jleft == 0) {
                 const int want = jnext >= a.ws->light_slot[x] ? kLightClaim : 1;
                 int j = 0;
@@ -724,10 +776,14 @@ void k_forces(KArgs a) {
             cwrap[lane] = ColWrap{incl - o.len1, o.src1 - (incl - o.len1)};
         }
 
-        const int P = a.cell_parts[c];
-        const int part = sgpr(it.part);
-        // part boundaries: nsrc split into P near-equal contiguous ranges (32-bit arithmetic)
+        // parts of the source list, nsrc split into P near-equal contiguous ranges (32-bit arithmetic): the item's
+        // one, or all of them in turn
+        const int split = sgpr(a.cell_parts[c]);
+        const bool whole = split < 0;
+        const int P = whole ? -split : split;
         const int pq = nsrc / P, pr = nsrc - pq * P;
+        part = whole ? (parts_left > 0 ? part + 1 : 0) : sgpr(it.part);
+        parts_left = whole ? P - 1 - part : 0;
         const int j0 = part * pq + min(part, pr);
         const int j1 = j0 + pq + (part < pr ? 1 : 0);
 
@@ -918,10 +974,23 @@ void k_forces(KArgs a) {
             }
             wave_lds_sync();
         }
+        // A whole list's parts are added up in order in the sink's slot, as k_finalize adds those of a split one.
+        const bool done = P <= 1 || (whole && part + 1 == P);
         double amax2 = 0.0;   // largest |a|^2 this lane writes (cells written here, not split ones)
         for (int idx = lane; idx < nt; idx += 64) {
             const int base = ((idx / S) * L * S + idx % S) * NC;
-            if (P <= 1) {
+            double *slot = nullptr;
+            if (P > 1) slot = a.partials + (int64_t)NC * (a.cell_pbase[c] + (int64_t)(whole ? 0 : part) * nc + t0 + idx);
+            if (whole) {
+#pragma unroll
+                for (int d = 0; d < NC; d++) {
+                    if constexpr (MODE == ABACUS_NF_SUM_FP32)
+                        redf[base + d] = (part > 0 ? (float)slot[d] : 0.f) + redf[base + d];
+                    else
+                        red[base + d] = (part > 0 ? slot[d] : 0.0) + red[base + d];
+                }
+            }
+            if (done) {
                 const int64_t i = a.perm[cs0 + t0 + idx];
                 double wr[3];   // the values written
 #pragma unroll
@@ -947,17 +1016,16 @@ void k_forces(KArgs a) {
                 const double m = norm2_written(wr[0], wr[1], wr[2]);
                 amax2 = m > amax2 ? m : amax2;
             } else {
-                double *out = a.partials + (int64_t)NC * (a.cell_pbase[c] + (int64_t)part * nc + t0 + idx);
 #pragma unroll
                 for (int d = 0; d < NC; d++) {
                     if constexpr (MODE == ABACUS_NF_SUM_FP32)
-                        out[d] = redf[base + d];
+                        slot[d] = redf[base + d];
                     else
-                        out[d] = red[base + d];
+                        slot[d] = red[base + d];
                 }
             }
         }
-        if (P <= 1) {   // per-cell maximum of |a|^2 (the input of the step-size criterion)
+        if (done) {   // per-cell maximum of |a|^2 (the input of the step-size criterion)
             amax2 = wave_max_f64(amax2);
             if (lane == 0 && amax2 > 0.0) cell_max(a.amax, c, amax2);
         }
@@ -1170,9 +1238,15 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
     if (e != hipSuccess || a.n_cells <= 0) return e;
     const int S = a.tune.sinks_per_lane, ML = a.tune.max_lanes;
     const unsigned gc = grid_for(a.n_cells, 256);
-    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(256), 0, st, a.wb, a.boxes, a.n_boxes, S,
-                       a.tune.part_sources, (int)a.shared_room, a.partial_capacity, a.item_capacity, a.n_total);
+    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(256), 0, st, a.ws, a.wb, a.boxes, a.n_boxes, S, a.tune.part_sources);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (a.short_room) {
+        hipLaunchKernelGGL(k_wl_bins, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
+                           a.n_cells, S, ML, a.wb, a.ws);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_wl_fit, dim3(1), dim3(64), 0, st, a.ws, a.partial_capacity, a.item_capacity);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_wl_count, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
                        a.n_cells, S, ML, a.wb, a.ws, a.cell_parts, a.cell_pbase);
     if ((e = hipGetLastError()) != hipSuccess) return e;

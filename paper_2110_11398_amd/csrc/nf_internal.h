@@ -72,6 +72,33 @@ __host__ __device__ inline int64_t box_items(int64_t n, int64_t n_cells) {
     return (n < n_cells ? n : n_cells) + n / 16 + n / 11 + (32 * n < 65536 ? 32 * n : 65536);
 }
 
+// Lists of a batch: the rooms of all its boxes, up to kRoomSlots slots (4.3 GB) and kRoomItems items, or those of the
+// largest box that n particles can make.  Where the boxes' rooms add up to more, items take whole source lists (all
+// parts of a cell one after the other, the same sums) until the rest fits, and one slot per particle is always
+// enough.  The sizes follow from the totals alone, so that a batch of the same totals never needs more.
+constexpr int64_t kRoomSlots = (int64_t)1 << 27, kRoomItems = (int64_t)1 << 24;
+struct ListRoom {
+    int64_t slots, items;
+};
+inline ListRoom list_room(int64_t n, int64_t n_cells, int64_t n_boxes) {
+    const int64_t each = 65536 + 256 * (int64_t)kFillItems;
+    const int64_t unsplit = (n < n_cells ? n : n_cells) + n / 16 + n / 11;
+    const int64_t all_slots = 2 * n + (64 * n < n_boxes * each ? 64 * n : n_boxes * each);
+    const int64_t all_items = unsplit + (32 * n < n_boxes * 65536 ? 32 * n : n_boxes * 65536);
+    const int64_t most_slots = 2 * n + each > kRoomSlots ? 2 * n + each : kRoomSlots;
+    const int64_t most_items = unsplit + 65536 > kRoomItems ? unsplit + 65536 : kRoomItems;
+    ListRoom r;
+    r.slots = all_slots < most_slots ? all_slots : most_slots;
+    r.items = all_items < most_items ? all_items : most_items;
+    if (r.items > INT32_MAX - 1) r.items = INT32_MAX - 1;
+    return r;
+}
+// The least lists that serve any batch of n particles in n_cells cells: every source list whole.
+inline ListRoom least_room(int64_t n, int64_t n_cells) {
+    const int64_t unsplit = (n < n_cells ? n : n_cells) + n / 16 + n / 11 + 65536;
+    return ListRoom{n, unsplit < INT32_MAX - 1 ? unsplit : INT32_MAX - 1};
+}
+
 // Work of one box in a forces call.
 struct WorkBox {
     unsigned long long pairs;       // sum over cells of n_c * sources(c)
@@ -87,6 +114,11 @@ struct WorkState {
     unsigned long long partial_slots; // partial slots of the split cells
     int32_t n_items;                  // items emitted (0 when a list outgrew its allocation)
     int32_t overflow;                 // non-zero when a list outgrew its capacity
+    int32_t whole_iters;              // cells of up to this many source iterations are not split over items
+    int32_t whole_bin;                // nor are those of length bins up to this one, where the lists are short
+    // where the boxes' rooms add up to more than the lists: what the lists hold with every cell whole, and what
+    // splitting the cells of a length bin adds
+    unsigned long long whole_slots, whole_items, bin_slots[kNumClasses], bin_items[kNumClasses];
     int32_t class_count[kNumClasses];
     int32_t class_fill[kNumClasses];
     int32_t light_slot[kQueues];      // first slot of each queue that holds a light item
@@ -252,11 +284,11 @@ struct ForcesArgs {
     WorkState *ws;
     WorkBox *wb;        // [n_boxes]
     int32_t *cell_nsrc;
-    int32_t *cell_parts;
-    int64_t *cell_pbase;   // first partial slot of a split cell (unset for others)
+    int32_t *cell_parts;   // parts of a cell's source list; negative: all of them in one item per tile
+    int64_t *cell_pbase;   // first partial slot of a cell of several parts (unset for others)
     double *partials;
     int64_t partial_capacity;
-    bool shared_room;      // the lists hold less than the boxes' own rooms: all parts are made longer alike
+    bool short_room;       // the boxes' rooms add up to more than the lists hold
     float *acc;
     double *acc64;   // FP64 accelerations instead of acc (nullptr: FP32 output)
     float *rho;      // density output (nullptr: forces only)

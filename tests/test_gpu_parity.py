@@ -482,6 +482,71 @@ def test_batched_boxes_equal_single_boxes_where_parts_fill_their_room(nf, form):
         at += K ** 3
 
 
+@pytest.mark.parametrize("mode,heavy", [(0, 0), (1, 0), (1, 30000), (2, 30000)])
+def test_batch_larger_than_the_lists(nf, mode, heavy):
+    """A batch whose boxes' rooms add up to more than the lists hold, with a heavy cell in some boxes: source lists that
+    stay whole and lists that are split give each box's forces as if it were alone, eagerly and replayed from a graph
+    with other work in between, and the lists take no more memory than they may."""
+    sizes = [(65536, 12)] * 37 + [(0, 5), (3001, 5)] + [(65536, 12)] * 32 + [(0, 3)]
+    assert sum(2 * n + min(32 * n, 65536) + min(32 * n, 1 << 22) for n, _ in sizes) > 1 << 27
+    boxes, total = [(n, 1.0, K) for n, K in sizes], sum(n for n, _ in sizes)
+    at = np.cumsum([0] + [n for n, _ in sizes])
+    gen_ = torch.Generator("cuda").manual_seed(3)
+    pos = torch.rand((total, 3), device="cuda", generator=gen_)
+    for i in (1, 30, 64):
+        pos[at[i]:at[i] + heavy] = 0.5 + 0.04 * pos[at[i]:at[i] + heavy]
+    eps, gm = [0.002] * len(sizes), [1.0 / 65536] * len(sizes)
+    c = nf.build_cells(pos, boxes, 1)
+    free = torch.cuda.mem_get_info()[0]
+    acc = c.forces(eps, gm, SPLINE, mode)
+    nf.sync()
+    assert free - torch.cuda.mem_get_info()[0] < 6e9
+    amax = c.copy(nf.ARRAY_CELL_AMAX2)
+    for i in [0, 1, 30, 36, 38, 39, 64, 70]:
+        n, K = sizes[i]
+        one = nf.build_cells(pos[at[i]:at[i + 1]].clone(), [(n, 1.0, K)], 1)
+        assert torch.equal(acc[at[i]:at[i + 1]], one.forces([eps[i]], [gm[i]], SPLINE, mode)), i
+        cells = sum(k ** 3 for _, k in sizes[:i])
+        assert torch.equal(amax[cells:cells + K ** 3], one.copy(nf.ARRAY_CELL_AMAX2)), i
+        one.free()
+    out = torch.empty_like(acc)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        nf.build_cells(pos, boxes, 1, cells=c)
+        c.forces(eps, gm, SPLINE, mode, out)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        assert c.interactions() > total
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, acc)
+    c.free()
+
+
+@pytest.mark.parametrize("form", ["fp32", "comp32", "fp64", "f64 output", "density"])
+def test_forces_do_not_depend_on_the_item_capacity(nf, form):
+    """Fewer items than the parts ask for: lists stay whole from the shortest up until the rest fits, and the sums are
+    the same to the bit, those of the densities and the maxima per cell too."""
+    rng = np.random.default_rng(17)
+    heavy = [0.3 + 0.03 * rng.random((n, 3)) + k for k, n in ((0.0, 9000), (0.25, 3000), (0.5, 700))]
+    pos = torch.from_numpy(np.concatenate([rng.random((20000, 3))] + heavy).astype(np.float32)).cuda()
+    n, mode, got = len(pos), {"fp32": 0, "fp64": 2}.get(form, 1), []
+    for cap in (0, 9000, 4000, 2000):
+        c = nf.build_cells(pos, [(n, 1.0, 8)], 2)
+        c.set_tuning(item_capacity=cap)
+        if form == "density":
+            out = c.forces_density([0.002], [1.0], [0.01], SPLINE, mode)
+        elif form == "f64 output":
+            out = (c.forces_f64([0.002], [1.0], SPLINE, mode),)
+        else:
+            out = (c.forces([0.002], [1.0], SPLINE, mode),)
+        nf.sync()
+        got.append((*out, c.copy(nf.ARRAY_CELL_AMAX2)))
+        c.free()
+    for g in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], g))
+
+
 def test_run_to_run_bit_identical(nf):
     w = gen.workload("clustered", side=64, K=16, n_halos=64)
     b = w.boxes[0]
