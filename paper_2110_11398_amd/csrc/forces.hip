@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
 // Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
 // at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
 // leaves the rest of the chip idle until it ends.  The length is at most the tuning's part_sources and at least
-// kMinPart, and longer where the box's own room (box_slots, box_items) is less than its parts would take: it
+// kMinPart (twice that where such parts still give kFewItems items), and longer where the box's own room (box_slots, box_items) is less than its parts would take: it
 // follows from the box alone, so a box gives bit-identical forces whatever batch it is in.
 //
 // What a batch decides is which cells are split over items at all.  A cell whose list is no longer than a wave's share
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void k_wl_plan(WorkState *__restrict__ ws, Wor
     for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
         const WorkBox w = wb[b];
         const int64_t n = boxes[b].n, K = boxes[b].K;
-        const long long want = capped(w.pairs / share), it = want < kMinPart ? kMinPart : want;
+        const long long want = capped(w.pairs / share), least = least_part(w.pairs, S), it = want < least ? least : want;
         // bounds at this length: slots <= n + slot_iters / length, items <= tiles + item_iters / length
         const double slots = (double)(w.slot_iters / it + 1), items = (double)(w.item_iters / it + 1);
         const double slot_room = (double)(box_slots(n) - n), item_room = (double)box_items(n, K * K * K) - (double)w.tiles;

@@ -52,12 +52,18 @@ constexpr int kLightClass = 47;
 constexpr int kLightClaim = 4;
 
 // Source lists are split so that a box gives at least about kFillItems items of equal cost (four for each wave the
-// chip holds at four per SIMD), into parts of at least kMinPart source iterations per lane.  Measured (force kernel
-// and finalize, leapfrog case of 262144 particles / Plummer box of 1000003 / batch of 48 boxes, ms): 8192 items 2.04
-// / 5.9 / 4.4, 16384 2.04 / 5.6 / 4.4, 32768 2.02 / 5.6 / 4.5; unsplit 7.9 / 12.2 / 4.3.  Shorter parts than
-// kMinPart cost more in set-up, partial sums and their reading than they balance (the batch: 4.4 at 128, 4.2 at 256).
-constexpr unsigned long long kFillItems = 16384;
+// chip holds at four per SIMD), into parts of at least kMinPart source iterations per lane, twice that where these
+// give kFewItems items.  Measured (force kernel and finalize, leapfrog case of 262144 particles / Plummer box of
+// 1000003, ms): 8192 items 2.04 / 5.9, 16384 2.04 / 5.6, 32768 2.02 / 5.6; unsplit 7.9 / 12.2.  Shorter parts than the
+// chip needs cost more in set-up and partial sums than they balance (forces of 13824 clustered particles / 32768
+// uniform / 512 boxes of the latter: 117 us / 170 us / 40.8 ms with parts of 256, 130 / 166 / 40.2 of 384, 145 / 182 /
+// 39.1 of 512).
+constexpr unsigned long long kFillItems = 16384, kFewItems = 2700;
 constexpr long long kMinPart = 256;
+__host__ __device__ inline long long least_part(unsigned long long pairs, int S) {
+    const long long few = (long long)(pairs / ((unsigned long long)(64 * S) * kFewItems));
+    return few < kMinPart ? kMinPart : (few > 2 * kMinPart ? 2 * kMinPart : few);
+}
 
 // Room of one box in the lists: the parts of its split source lists are made longer until they fit, so that a box is
 // cut in the same way whatever batch it is in.  Partial slots, one per sink and part: the parts that fill the chip

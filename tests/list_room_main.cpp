@@ -1,5 +1,6 @@
 // Prints the lists the force pass holds for batches of boxes, for the host-side test: one line per batch with the
-// particles, the cells, slots and items of the lists, those the boxes' rooms add up to, and the least lists.
+// particles, the cells, slots and items of the lists, those the boxes' rooms add up to, and the least lists; then one
+// line per pair count and sinks per lane with the least length of a source part.
 #include <cstdio>
 #include <vector>
 
@@ -28,5 +29,9 @@ int main() {
         printf("%lld %lld %lld %lld %lld %lld %lld %lld %lld\n", boxes, n, cells, (long long)r.slots,
                (long long)r.items, slots, items, (long long)l.slots, (long long)l.items);
     }
+    printf("\n");
+    for (int S : {1, 2, 4})
+        for (unsigned long long pairs = 0; pairs < (1ull << 45); pairs = 2 * pairs + 1234567)
+            printf("%d %llu %lld\n", S, pairs, anf::least_part(pairs, S));
     return 0;
 }

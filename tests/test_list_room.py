@@ -14,7 +14,7 @@ SLOT, ITEM = 32, 16     # bytes
 
 
 @pytest.fixture(scope="module")
-def rooms(tmp_path_factory):
+def printed(tmp_path_factory):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
@@ -22,9 +22,13 @@ def rooms(tmp_path_factory):
     r = subprocess.run([hipcc, "-O1", "-o", exe, os.path.join(HERE, "list_room_main.cpp")], capture_output=True,
                        text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    out = subprocess.run([exe], capture_output=True, text=True, check=True).stdout
+    return subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split("\n\n")
+
+
+@pytest.fixture(scope="module")
+def rooms(printed):
     names = ("boxes", "n", "cells", "slots", "items", "box_slots", "box_items", "least_slots", "least_items")
-    return [dict(zip(names, map(int, line.split()))) for line in out.splitlines()]
+    return [dict(zip(names, map(int, line.split()))) for line in printed[0].splitlines()]
 
 
 def test_lists_take_64_bytes_a_particle_and_a_constant(rooms):
@@ -44,3 +48,13 @@ def test_least_lists_hold_a_slot_per_particle_and_every_unsplit_item(rooms):
         assert r["least_slots"] == r["n"], r
         unsplit = min(r["n"], r["cells"]) + r["n"] // 64 + r["n"] // 11
         assert r["least_items"] >= min(unsplit, 2 ** 31 - 2), r
+
+
+def test_parts_are_short_only_where_the_box_gives_few_items(printed):
+    for line in printed[1].splitlines():
+        S, pairs, least = map(int, line.split())
+        assert 256 <= least <= 512, line
+        if least > 256:      # parts of this length still give about 2700 items
+            assert pairs // (64 * S * least) >= 2700, line
+        if least < 512:
+            assert pairs // (64 * S * (least + 1)) < 2700, line
