@@ -351,6 +351,12 @@ int abacus_nf_build_cells(const float *pos, int64_t n_total, const abacus_nf_box
         m.add_bytes(h->scan_temp, scan_temp_bytes(std::max(cc, cn)));
         if (!m.alloc(h->sort_block)) {
             free_sort_buffers(h);
+            // no buffers, no batch: every call on the handle is refused until a build succeeds
+            h->built = h->amax_valid = false;
+            h->n_total = h->n_cells = 0;
+            h->n_boxes = 0;
+            h->boxes.clear();
+            h->cell_base.clear();
             if (fresh) delete h;
             return ABACUS_NF_ENOMEM;
         }
