@@ -137,6 +137,7 @@ class Cells:
         self._h = ctypes.c_void_p(None)
         self.boxes: List[Tuple[int, float, int]] = []
         self.n_total = 0
+        self._own_sinks = False   # sinks per lane were set here or by a search
 
     # -- C ABI wrappers
     def build(self, pos, boxes: Iterable[Tuple[int, float, int]], R: int = 2, stream=None) -> "Cells":
@@ -336,12 +337,17 @@ class Cells:
 
     def set_tuning(self, **kw):
         t = self.get_tuning() if kw else Tuning()
+        own = bool(kw) and bool(kw.get("sinks_per_lane", self._own_sinks))
+        if not own:
+            t.sinks_per_lane = 0   # stays the library's choice, which depends on the summation mode
         for k, v in kw.items():
             setattr(t, k, int(v))
         _check(library().abacus_nf_set_tuning(self._h, ctypes.byref(t)), "abacus_nf_set_tuning")
+        self._own_sinks = own
 
     def reset_tuning(self):
         _check(library().abacus_nf_set_tuning(self._h, None), "abacus_nf_set_tuning")
+        self._own_sinks = False
 
     def get_tuning(self) -> Tuning:
         t = Tuning()
@@ -359,6 +365,7 @@ class Cells:
                                           ctypes.c_void_p(_stream_handle(stream)), int(reps),
                                           cache_path.encode() if cache_path else None, ctypes.byref(t))
         _check(rc, "abacus_nf_autotune")
+        self._own_sinks = True
         return t
 
     def autotune_density(self, eps, gm, b, kind=SPLINE, mode=SUM_COMP32, out=None, rho=None, reps: int = 2,
@@ -376,6 +383,7 @@ class Cells:
                                                   ctypes.c_void_p(_stream_handle(stream)), int(reps),
                                                   cache_path.encode() if cache_path else None, ctypes.byref(t))
         _check(rc, "abacus_nf_autotune_density")
+        self._own_sinks = True
         return t
 
     def set_timing(self, on: bool = True):

@@ -22,6 +22,7 @@ struct abacus_nf_cells_s {
     std::vector<abacus_nf_box> boxes;
     std::vector<int32_t> cell_base;
     abacus_nf_tuning tune{};
+    bool default_sinks = true;   // sinks per lane are the library's choice
 
     // one device allocation each for the buffers of build_cells and of the force pass, cut up by Carver
     void *sort_block = nullptr, *work_block = nullptr;
@@ -208,11 +209,17 @@ int key_bits(int64_t n_cells) {
     return b;
 }
 
+// Sinks per lane of FP64 sums by default: four would spill 57 registers a lane with the spline, two none (spline,
+// clustered, 8.4 million / 1.05 million particles: 29.8 / 2.33 ms at two, 30.4 / 2.48 at four; with the density 33.4 /
+// 2.60 and 35.7 / 2.96; 1.05 million in sparse cells 1.17 and 1.60).
+constexpr int kSinksFp64 = 2;
+
 abacus_nf_tuning default_tuning() {
     abacus_nf_tuning t;
     memset(&t, 0, sizeof(t));
     // four sinks per lane and two sources a step: eight reciprocal square roots issued together (clustered box of
-    // 256^3 particles: 99.9 ms; two sinks and two or four sources 104, four sinks and one source 104)
+    // 256^3 particles: 99.9 ms; two sinks and two or four sources 104, four sinks and one source 104); FP64 sums
+    // take kSinksFp64
     t.sinks_per_lane = 4;
     t.chunk = 256;
     t.unroll = 2;
@@ -453,6 +460,13 @@ static int ensure_work_buffers(abacus_nf_cells_s *h) {
     return ABACUS_NF_ENOMEM;
 }
 
+// The handle's tuning, as it is for a summation mode.
+static abacus_nf_tuning tuning_of(const abacus_nf_cells_s *h, abacus_nf_sum mode) {
+    abacus_nf_tuning t = h->tune;
+    if (h->default_sinks && mode == ABACUS_NF_SUM_FP64) t.sinks_per_lane = kSinksFp64;
+    return t;
+}
+
 static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf_sum mode, float *acc, int *err) {
     ForcesArgs a;
     memset(&a, 0, sizeof(a));
@@ -487,7 +501,7 @@ static ForcesArgs make_args(abacus_nf_cells_s *h, abacus_nf_kind kind, abacus_nf
     a.err = err;
     a.kind = kind;
     a.mode = mode;
-    a.tune = h->tune;
+    a.tune = tuning_of(h, mode);
     return a;
 }
 
@@ -518,10 +532,10 @@ static int forces_impl(abacus_nf_cells h, const double *eps, abacus_nf_kind kind
     ForcesArgs a = make_args(h, kind, mode, acc, err);
     a.acc64 = acc64;
     a.rho = kde_b ? rho : nullptr;
-    const int key[8] = {(int)kind, (int)mode, h->tune.sinks_per_lane, h->tune.unroll, h->tune.chunk,
-                        h->tune.waves_per_cu, dev * 2 + (kde_b ? 1 : 0), h->tune.occupancy};
+    const int key[8] = {(int)kind, (int)mode, a.tune.sinks_per_lane, a.tune.unroll, a.tune.chunk,
+                        a.tune.waves_per_cu, dev * 2 + (kde_b ? 1 : 0), a.tune.occupancy};
     if (memcmp(key, h->grid_key, sizeof(key)) != 0 || h->grid <= 0) {
-        h->grid = forces_grid(h->tune, kind, mode, kde_b != nullptr, dev);
+        h->grid = forces_grid(a.tune, kind, mode, kde_b != nullptr, dev);
         memcpy(h->grid_key, key, sizeof(key));
     }
     a.grid = h->grid;
@@ -703,6 +717,8 @@ int abacus_nf_timestep(abacus_nf_cells h, const float *vel, const float *acc, do
 namespace anf {
 
 int handle_boxes(abacus_nf_cells h) { return h ? h->n_boxes : 0; }
+
+bool handle_default_sinks(abacus_nf_cells h) { return h && h->default_sinks; }
 
 int timestep_arguments(abacus_nf_cells h, const float *vel, const float *acc, double eta, double *dt_out) {
     return timestep_args(h, vel, acc, eta, dt_out);
@@ -904,6 +920,7 @@ int abacus_nf_set_tuning(abacus_nf_cells h, const abacus_nf_tuning *tuning) {
     abacus_nf_tuning t;
     if (!resolve_tuning(tuning, &t)) return ABACUS_NF_EINVAL;
     h->tune = t;
+    h->default_sinks = !tuning || tuning->sinks_per_lane == 0;
     return ABACUS_NF_OK;
 }
 

@@ -95,6 +95,7 @@ int tune(abacus_nf_cells h, const double *eps, abacus_nf_kind kind, const double
     abacus_nf_tuning cur;
     int rc = abacus_nf_get_tuning(h, &cur);
     if (rc) return rc;
+    if (anf::handle_default_sinks(h)) cur.sinks_per_lane = 0;   // as it was, should the search fail
     const std::string key = cache_key(h, kind, mode, kde_b != nullptr);
     if (cache_path) {
         auto m = read_cache(cache_path);

@@ -341,7 +341,8 @@ size_t timestep_min_offset(int n_boxes);
 int timestep_with_buffers(abacus_nf_cells h, const float *vel, const float *acc, double eta, double *dt_out,
                           double *partials, size_t partial_doubles, unsigned long long *dmin, size_t dmin_words,
                           void *hip_stream);
-int handle_boxes(abacus_nf_cells h);   // boxes of a handle (0 for NULL)
+int handle_boxes(abacus_nf_cells h);
+bool handle_default_sinks(abacus_nf_cells h);   // sinks per lane were not set by the caller   // boxes of a handle (0 for NULL)
 // The argument and state checks of abacus_nf_timestep alone (no HIP call).
 int timestep_arguments(abacus_nf_cells h, const float *vel, const float *acc, double eta, double *dt_out);
 

@@ -862,6 +862,22 @@ def test_autotune_search_writes_the_cache_and_skips_overflowing_candidates(nf, t
     c.free()
 
 
+def test_default_sinks_of_fp64_sums_survive_other_settings(nf):
+    """Setting another field through the binding leaves sinks per lane to the library: two for FP64 sums."""
+    p = torch.rand((20000, 3), device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    c = nf.build_cells(p, [(20000, 1.0, 7)], 2)
+    got = []
+    for kw in ({}, dict(part_sources=2048), dict(sinks_per_lane=2), None, dict(unroll=2)):
+        c.reset_tuning() if kw is None else c.set_tuning(**kw)
+        got.append(c.forces_f64([0.002], [1.0], SPLINE, 2))
+    c.set_tuning(sinks_per_lane=4)
+    four = c.forces_f64([0.002], [1.0], SPLINE, 2)
+    nf.sync()
+    assert all(torch.equal(g, got[0]) for g in got)
+    assert not torch.equal(four, got[0])
+    c.free()
+
+
 def test_bad_tuning_is_rejected(nf):
     p = torch.rand((100, 3), device="cuda")
     c = nf.build_cells(p, [(100, 1.0, 5)], 2)

@@ -1,4 +1,4 @@
-"""Handles when device memory runs out (no GPU).
+"""Handles when device memory runs out, and their tuning by summation mode (no GPU).
 
 The library's host side is compiled as it is, without its kernels, and linked with a stand-in for the HIP runtime whose
 device memory has a budget.  A build that cannot get its buffers leaves a handle that every call refuses (ESTATE)
@@ -48,3 +48,7 @@ def test_the_force_pass_takes_the_least_lists_where_memory_is_short(lines):
     assert lines[6] == f"build {OK} forces {OK} slots {want} short 1 again {OK} null=0"
     assert lines[7] == f"build {OK} forces {OK} slots {least} short 1 again {OK} null=0"
     assert lines[8] == f"build {OK} forces {ENOMEM} again {OK} null=0"
+
+
+def test_fp64_sums_take_two_sinks_per_lane_unless_set(lines):
+    assert lines[10:] == ["sinks 4 4 2 get 4", "sinks 4 4 4 get 4", "sinks 1 1 1 get 1", "sinks 4 4 2 get 4"]
