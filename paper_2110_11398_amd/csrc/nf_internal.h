@@ -87,11 +87,13 @@ struct ListRoom {
     int64_t slots, items;
 };
 inline ListRoom list_room(int64_t n, int64_t n_cells, int64_t n_boxes) {
-    const int64_t each = 65536 + 256 * (int64_t)kFillItems;
-    const int64_t unsplit = (n < n_cells ? n : n_cells) + n / 16 + n / 11;
-    const int64_t all_slots = 2 * n + (64 * n < n_boxes * each ? 64 * n : n_boxes * each);
-    const int64_t all_items = unsplit + (32 * n < n_boxes * 65536 ? 32 * n : n_boxes * 65536);
-    const int64_t most_slots = 2 * n + each > kRoomSlots ? 2 * n + each : kRoomSlots;
+    const int64_t fill = 256 * (int64_t)kFillItems;
+    const auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
+    const int64_t unsplit = least(n, n_cells) + n / 16 + n / 11;
+    // the most that n particles in so many boxes can ask for
+    const int64_t all_slots = 2 * n + least(32 * n, n_boxes * 65536) + least(32 * n, n_boxes * fill);
+    const int64_t all_items = unsplit + least(32 * n, n_boxes * 65536);
+    const int64_t most_slots = 2 * n + 65536 + fill > kRoomSlots ? 2 * n + 65536 + fill : kRoomSlots;
     const int64_t most_items = unsplit + 65536 > kRoomItems ? unsplit + 65536 : kRoomItems;
     ListRoom r;
     r.slots = all_slots < most_slots ? all_slots : most_slots;
