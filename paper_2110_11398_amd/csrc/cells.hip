@@ -10,14 +10,15 @@
 //   k_bin          cell of every particle (FP64 cell rule) and a tile histogram of its leading digit
 //   k_seg_scatter  as partition: stable scatter by the leading digit (up to 8 bits) of coordinates, input index and
 //                  cell; every later step then works inside one bucket, whose few MB stay in cache
-//   k_seg_hist,    per bucket: digit counts of every tile, their exclusive sums over the tiles and the digits
-//   k_seg_scan
+//   k_seg_hist,    per bucket: digit counts of every tile, their exclusive sums over runs of tiles, and the first slots
+//   k_seg_sums,    of the digits in every run
+//   k_seg_base
 //   k_seg_scatter  stable scatter inside the buckets; the last one writes the sorted keys, the permutation and
 //                  the cell-relative coordinates in cell widths, FP64 -> FP32
 //
 // Where the last digit spans the whole cell index inside a bucket (keys of up to 19 bits in large calls), its sums
 // are the cell offsets; longer keys take one more digit before it, and k_run_ends with a max-scan the offsets.
-// Small calls skip the partition: one bucket, one digit.
+// Small calls and boxes of few cells skip the partition: one bucket, one digit.
 //
 // Bound by memory: coordinates move in order three times (44 bytes read and 44 written per particle with the keys),
 // against one random 12-byte gather, a cache line each, when only keys and indices were sorted.  Clustered box of
@@ -199,44 +200,66 @@ hipError_t scan_impl(const T *in, T *out, int64_t n, bool inclusive, T identity,
 // ---------------------------------------------------------------- sort by cell
 
 __global__ __launch_bounds__(kMaxBuckets) void k_buckets(const uint32_t *__restrict__ toff, int ntiles, int nb, int64_t n,
-                                                         int tile, Buckets *__restrict__ o) {
-    __shared__ int32_t wsum[kMaxBuckets / 64];
+                                                         int tile, int run_shift, Buckets *__restrict__ o) {
+    __shared__ int32_t wsum[2][kMaxBuckets / 64];
     const int b = threadIdx.x, lane = b & 63;
     const uint32_t lo = b < nb ? toff[(int64_t)b * ntiles] : (uint32_t)n;
     const uint32_t hi = b + 1 < nb ? toff[(int64_t)(b + 1) * ntiles] : (uint32_t)n;
     const int t = b < nb ? (hi > lo ? (int)((hi - lo + tile - 1) / tile) : 1) : 0;
-    int incl = t;
+    const int r = (t + (1 << run_shift) - 1) >> run_shift;
+    int tiles = t, runs = r;
     for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(incl, off);
-        if (lane >= off) incl += y;
+        const int y = __shfl_up(tiles, off), z = __shfl_up(runs, off);
+        if (lane >= off) {
+            tiles += y;
+            runs += z;
+        }
     }
-    if (lane == 63) wsum[b >> 6] = incl;
+    if (lane == 63) {
+        wsum[0][b >> 6] = tiles;
+        wsum[1][b >> 6] = runs;
+    }
     __syncthreads();
-    for (int w = 0; w < (b >> 6); w++) incl += wsum[w];
+    for (int w = 0; w < (b >> 6); w++) {
+        tiles += wsum[0][w];
+        runs += wsum[1][w];
+    }
     o->start[b] = lo;
-    o->tile[b] = incl - t;
+    o->tile[b] = tiles - t;
+    o->run[b] = runs - r;
     if (b == kMaxBuckets - 1) {
         o->start[kMaxBuckets] = (uint32_t)n;
-        o->tile[kMaxBuckets] = incl;
+        o->tile[kMaxBuckets] = tiles;
+        o->run[kMaxBuckets] = runs;
     }
 }
 
-// Bucket, first slot and number of slots of tile g (bk null: one bucket of n slots); false past the last tile.
-__device__ inline bool seg_tile(const Buckets *__restrict__ bk, int64_t n, int tile, int g, int &bucket, int64_t &base,
-                                int &count) {
-    bucket = 0;
+// The last of the nb buckets whose first tile or run is at most g: every thread looks at a bucket or two (a binary search
+// by each thread waits for nine loads in turn).  The whole workgroup.
+template <int THREADS>
+__device__ inline int bucket_at(const int32_t *__restrict__ first, int nb, int g) {
+    int count = 0;
+    for (int i = 0; i < nb; i += THREADS) {
+        const int b = i + (int)threadIdx.x;
+        count += __syncthreads_count(b < nb && first[b] <= g);
+    }
+    return count - 1;
+}
+
+// Run, first slot and number of slots of tile g (bk null: one bucket of n slots); false past the last tile.  The whole
+// workgroup.
+template <int THREADS>
+__device__ inline bool seg_tile(const Buckets *__restrict__ bk, int nb, int64_t n, int tile, int run_shift, int g, int &run,
+                                int64_t &base, int &count) {
+    run = g >> run_shift;
     int64_t end = n;
     base = (int64_t)g * tile;
     if (bk) {
         if (g >= bk->tile[kMaxBuckets]) return false;
-        int lo = 0, hi = kMaxBuckets - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (bk->tile[mid] <= g) lo = mid; else hi = mid - 1;
-        }
-        bucket = lo;
-        base = (int64_t)bk->start[lo] + (int64_t)(g - bk->tile[lo]) * tile;
-        end = bk->start[lo + 1];
+        const int b = bucket_at<THREADS>(bk->tile, nb, g), in = g - bk->tile[b];
+        run = bk->run[b] + (in >> run_shift);
+        base = (int64_t)bk->start[b] + (int64_t)in * tile;
+        end = bk->start[b + 1];
     }
     const int64_t left = end - base;
     count = left < tile ? (left > 0 ? (int)left : 0) : tile;
@@ -245,13 +268,13 @@ __device__ inline bool seg_tile(const Buckets *__restrict__ bk, int64_t n, int t
 
 template <int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_seg_hist(const int32_t *__restrict__ keys, int64_t n,
-                                                      const Buckets *__restrict__ bk, int shift, int bits,
+                                                      const Buckets *__restrict__ bk, int nb, int shift, int bits,
                                                       uint32_t *__restrict__ rows) {
     extern __shared__ uint32_t smem_u32[];
     uint32_t *h = smem_u32;
-    int bucket, count;
+    int run, count;
     int64_t base;
-    if (!seg_tile(bk, n, THREADS * ITEMS, blockIdx.x, bucket, base, count)) return;
+    if (!seg_tile<THREADS>(bk, nb, n, THREADS * ITEMS, 0, blockIdx.x, run, base, count)) return;
     const int D = 1 << bits, tid = threadIdx.x;
     for (int d = tid; d < D; d += THREADS) h[d] = 0;
     __syncthreads();
@@ -264,44 +287,44 @@ __global__ __launch_bounds__(THREADS) void k_seg_hist(const int32_t *__restrict_
     for (int d = tid; d < D; d += THREADS) rows[(int64_t)blockIdx.x * D + d] = h[d];
 }
 
-// One workgroup per bucket: the rows of its tiles become exclusive sums over the tiles, four digits to a thread and
-// the loads of eight rows in flight, and dbase the first slot of every digit.  With cell_start, bits that end the
-// key: slot of every cell.
-constexpr int kSegScanThreads = 1 << (kLastBits - 2);
-__global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(uint32_t *__restrict__ rows, uint32_t *__restrict__ dbase,
-                                                              const Buckets *__restrict__ bk, int64_t n, int ntiles,
-                                                              int bits, int32_t *__restrict__ cell_start,
-                                                              int64_t n_cells) {
-    __shared__ uint32_t wsum[kSegScanThreads / 64];
-    const int Q = 1 << (bits - 2), tid = threadIdx.x, b = blockIdx.x, lane = tid & 63;   // Q groups of four digits
-    const int t0 = bk ? bk->tile[b] : 0, t1 = bk ? bk->tile[b + 1] : ntiles;
-    uint4 run = make_uint4(0, 0, 0, 0);   // then the totals of this thread's digits
-    auto add = [](uint4 &x, const uint4 &y) {
-        x.x += y.x;
-        x.y += y.y;
-        x.z += y.z;
-        x.w += y.w;
-    };
-    if (tid < Q) {
-        uint4 *col = (uint4 *)rows + (int64_t)t0 * Q + tid;
-        int t = t0;
-        for (; t + 8 <= t1; t += 8, col += 8 * (int64_t)Q) {
-            uint4 v[8];
+__device__ inline void add4(uint4 &x, const uint4 &y) {
+    x.x += y.x;
+    x.y += y.y;
+    x.z += y.z;
+    x.w += y.w;
+}
+
+// Exclusive sums down a column of rows [t0, t1) of Q groups of four counts each, in place, the loads of eight rows in
+// flight; returns the totals.
+__device__ inline uint4 scan_rows(uint4 *col, int t0, int t1, int64_t Q) {
+    uint4 run = make_uint4(0, 0, 0, 0);
+    int t = t0;
+    for (; t + 8 <= t1; t += 8, col += 8 * Q) {
+        uint4 v[8];
 #pragma unroll
-            for (int q = 0; q < 8; q++) v[q] = col[q * (int64_t)Q];
+        for (int q = 0; q < 8; q++) v[q] = col[q * Q];
 #pragma unroll
-            for (int q = 0; q < 8; q++) {
-                col[q * (int64_t)Q] = run;
-                add(run, v[q]);
-            }
-        }
-        for (; t < t1; t++, col += Q) {
-            const uint4 v = *col;
-            *col = run;
-            add(run, v);
+        for (int q = 0; q < 8; q++) {
+            col[q * Q] = run;
+            add4(run, v[q]);
         }
     }
-    const uint32_t s = run.x + run.y + run.z + run.w;
+    for (; t < t1; t++, col += Q) {
+        const uint4 v = *col;
+        *col = run;
+        add4(run, v);
+    }
+    return run;
+}
+
+// First slots of four digits of bucket b, from the digits' totals; with cell_start, bits that end the key: slot of
+// every cell.  The whole workgroup.
+constexpr int kSegScanThreads = 1 << (kLastBits - 2);
+__device__ inline uint4 digit_starts(const uint4 &sum, int b, uint32_t start, int Q, int64_t n,
+                                     int32_t *__restrict__ cell_start, int64_t n_cells) {
+    __shared__ uint32_t wsum[kSegScanThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t s = sum.x + sum.y + sum.z + sum.w;
     uint32_t incl = s;
     for (int off = 1; off < 64; off <<= 1) {
         const uint32_t y = __shfl_up(incl, off);
@@ -309,19 +332,59 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(uint32_t *__restri
     }
     if (lane == 63) wsum[tid >> 6] = incl;
     __syncthreads();
-    if (tid < Q) {
-        uint32_t first = (bk ? bk->start[b] : 0u) + incl - s;
-        for (int w = 0; w < (tid >> 6); w++) first += wsum[w];
-        const uint4 o = make_uint4(first, first + run.x, first + run.x + run.y, first + run.x + run.y + run.z);
-        const int64_t g = (int64_t)b * Q + tid;
-        ((uint4 *)dbase)[g] = o;
-        if (cell_start) {
-            const uint32_t v[4] = {o.x, o.y, o.z, o.w};
-            for (int q = 0; q < 4; q++)
-                if (4 * g + q < n_cells) cell_start[4 * g + q] = (int32_t)v[q];
-        }
+    uint32_t first = start + incl - s;
+    for (int w = 0; w < (tid >> 6); w++) first += wsum[w];
+    const uint4 o = make_uint4(first, first + sum.x, first + sum.x + sum.y, first + sum.x + sum.y + sum.z);
+    if (cell_start && tid < Q) {
+        const int64_t g = 4 * ((int64_t)b * Q + tid);
+        const uint32_t v[4] = {o.x, o.y, o.z, o.w};
+        for (int q = 0; q < 4; q++)
+            if (g + q < n_cells) cell_start[g + q] = (int32_t)v[q];
     }
     if (cell_start && b == 0 && tid == 0) cell_start[n_cells] = (int32_t)n;
+    return o;
+}
+
+// One workgroup per run of tiles: their rows of digit counts become exclusive sums over the run, four digits to a
+// thread, and dbase, per run, the digits' totals.  Where every bucket is one run (`single`) dbase gets the first slots
+// at once.
+__global__ __launch_bounds__(kSegScanThreads) void k_seg_sums(uint32_t *__restrict__ rows, uint32_t *__restrict__ dbase,
+                                                              const Buckets *__restrict__ bk, int nb, int64_t n,
+                                                              int ntiles, int run_shift, int bits, int single,
+                                                              int32_t *__restrict__ cell_start, int64_t n_cells) {
+    const int Q = 1 << (bits - 2), tid = threadIdx.x, g = blockIdx.x;   // Q groups of four digits
+    int b = 0, t0 = g << run_shift, end = ntiles;
+    if (bk) {
+        if (g >= bk->run[kMaxBuckets]) return;
+        b = single ? g : bucket_at<kSegScanThreads>(bk->run, nb, g);
+        t0 = bk->tile[b] + ((g - bk->run[b]) << run_shift);
+        end = bk->tile[b + 1];
+    }
+    const int t1 = end - t0 < (1 << run_shift) ? end : t0 + (1 << run_shift);
+    uint4 sum = make_uint4(0, 0, 0, 0);
+    if (tid < Q) sum = scan_rows((uint4 *)rows + (int64_t)t0 * Q + tid, t0, t1, Q);
+    if (single) sum = digit_starts(sum, b, bk ? bk->start[b] : 0u, Q, n, cell_start, n_cells);
+    if (tid < Q) ((uint4 *)dbase)[(int64_t)g * Q + tid] = sum;
+}
+
+// One workgroup per bucket: the totals of its runs become the first slots of the digits in each run.
+__global__ __launch_bounds__(kSegScanThreads) void k_seg_base(uint32_t *__restrict__ dbase,
+                                                              const Buckets *__restrict__ bk, int64_t n, int nruns,
+                                                              int bits, int32_t *__restrict__ cell_start,
+                                                              int64_t n_cells) {
+    const int Q = 1 << (bits - 2), tid = threadIdx.x, b = blockIdx.x;
+    const int r0 = bk ? bk->run[b] : 0, r1 = bk ? bk->run[b + 1] : nruns;
+    uint4 *col = (uint4 *)dbase + (int64_t)r0 * Q + tid;
+    uint4 sum = make_uint4(0, 0, 0, 0);
+    if (tid < Q) sum = scan_rows(col, r0, r1, Q);
+    const uint4 first = digit_starts(sum, b, bk ? bk->start[b] : 0u, Q, n, cell_start, n_cells);
+    if (tid < Q)
+#pragma unroll 8
+        for (int r = r0; r < r1; r++, col += Q) {
+            uint4 v = *col;
+            add4(v, first);
+            *col = v;
+        }
 }
 
 // What a scatter reads and writes.
@@ -336,13 +399,14 @@ struct SegArgs {
     const int32_t *kin;
     const float *pos;            // kSegPart, kSegLastPos
     const float4 *pay;           // kSegMid, kSegLast: x, y, z, input index (bits)
-    const uint32_t *rows;        // per tile and digit: first slot among the digit's (kSegPart: absolute, [digit][tile])
-    const uint32_t *dbase;       // per bucket and digit: first slot
+    const uint32_t *rows;        // per tile and digit: first slot among the run's (kSegPart: absolute, [digit][tile])
+    const uint32_t *dbase;       // per run and digit: first slot
     const Buckets *bk;
+    int nb;                      // buckets
     const BoxDev *boxes;
     int n_boxes;
     int64_t n;
-    int shift, bits;
+    int shift, bits, run_shift;
     int32_t *kout;
     int32_t *vout;               // last scatter: permutation
     float4 *out;                 // coordinates, or spos in the last scatter
@@ -388,9 +452,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS
     uint32_t *wsum = gd + D;                              // [WAVES]
     uint16_t *wcnt = (uint16_t *)(wsum + WAVES);          // [WAVES][D] counts, then tile positions
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    int bucket, count;
+    int run_of, count;
     int64_t base;
-    if (!seg_tile(OUT == kSegPart || OUT == kSegLastPos ? nullptr : a.bk, a.n, TILE, blockIdx.x, bucket, base, count))
+    if (!seg_tile<THREADS>(OUT == kSegPart || OUT == kSegLastPos ? nullptr : a.bk, a.nb, a.n, TILE, a.run_shift, blockIdx.x,
+                           run_of, base, count))
         return;
     for (int d = tid; d < WAVES * D / 2; d += THREADS) ((uint32_t *)wcnt)[d] = 0;
     __syncthreads();
@@ -467,7 +532,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS
         const int d = tid * per + q;
         if (d < D) {
             const uint32_t first = OUT == kSegPart ? a.rows[(int64_t)d * gridDim.x + blockIdx.x]
-                                                   : a.rows[(int64_t)blockIdx.x * D + d] + a.dbase[(int64_t)bucket * D + d];
+                                                   : a.rows[(int64_t)blockIdx.x * D + d] + a.dbase[(int64_t)run_of * D + d];
             gd[d] = first - run;
             for (int v = 0; v < WAVES; v++) {
                 const uint32_t c = wcnt[v * D + d];
@@ -599,27 +664,40 @@ hipError_t sort_impl(const SortArgs &a, const SortPlan &pl, int bits, int32_t **
     s.rows = rows;
     s.dbase = dbase;
     s.bk = nullptr;
+    s.nb = 1 << pl.part;
     s.boxes = a.boxes;
     s.n_boxes = a.n_boxes;
     s.n = n;
     s.shift = 0;
     s.bits = pl.last;
+    s.run_shift = run_shift(n);
     s.vout = a.perm;
     s.out = a.spos;
     *have_starts = pl.mid == 0;
+    const int nb = 1 << pl.part, shift_runs = s.run_shift;
+    // first slots of a digit of nbits bits from the tiles' counts
+    auto sums = [&](const Buckets *buckets, int nbits, bool starts) {
+        const int runs = buckets ? (ntiles >> shift_runs) + nb : (int)((ntiles + ((int64_t)1 << shift_runs) - 1) >> shift_runs);
+        const bool single = ntiles <= (1 << shift_runs);
+        int32_t *cell_start = starts ? a.cell_start : nullptr;
+        hipLaunchKernelGGL(k_seg_sums, dim3(runs), dim3(kSegScanThreads), 0, st, rows, dbase, buckets, nb, n, ntiles,
+                           shift_runs, nbits, (int)single, cell_start, a.n_cells);
+        hipError_t r = hipGetLastError();
+        if (r != hipSuccess || single) return r;
+        hipLaunchKernelGGL(k_seg_base, dim3(buckets ? nb : 1), dim3(kSegScanThreads), 0, st, dbase, buckets, n, runs, nbits,
+                           cell_start, a.n_cells);
+        return hipGetLastError();
+    };
     if (!pl.part) {
-        hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(kSegScanThreads), 0, st, rows, dbase, (const Buckets *)nullptr, n,
-                           ntiles, pl.last, a.cell_start, a.n_cells);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = sums(nullptr, pl.last, true)) != hipSuccess) return e;
         s.kout = *keys_out = a.keys_b;
         return scatter<THREADS, ITEMS, kSegLastPos>(s, ntiles, st);
     }
-    const int nb = 1 << pl.part;
     uint32_t *toff = rows + (size_t)nb * ntiles;
     char *scan_tmp = (char *)(((uintptr_t)(toff + (size_t)nb * ntiles) + 255) & ~(uintptr_t)255);
     e = scan_impl<uint32_t, OpAdd>(rows, toff, (int64_t)nb * ntiles, false, 0u, scan_tmp, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_buckets, dim3(1), dim3(kMaxBuckets), 0, st, toff, ntiles, nb, n, TILE, bk);
+    hipLaunchKernelGGL(k_buckets, dim3(1), dim3(kMaxBuckets), 0, st, toff, ntiles, nb, n, TILE, shift_runs, bk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     SegArgs q = s;
     q.rows = toff;
@@ -633,12 +711,10 @@ hipError_t sort_impl(const SortArgs &a, const SortPlan &pl, int bits, int32_t **
     const unsigned grid = (unsigned)(ntiles + nb);   // at least the tiles of all buckets
     auto digit = [&](const int32_t *keys, int shift, int nbits, bool starts) {
         hipLaunchKernelGGL((k_seg_hist<THREADS, ITEMS>), dim3(grid), dim3(THREADS), sizeof(uint32_t) << nbits, st, keys,
-                           n, bk, shift, nbits, rows);
+                           n, bk, nb, shift, nbits, rows);
         hipError_t r = hipGetLastError();
         if (r != hipSuccess) return r;
-        hipLaunchKernelGGL(k_seg_scan, dim3(nb), dim3(kSegScanThreads), 0, st, rows, dbase, bk, n, 0, nbits,
-                           starts ? a.cell_start : (int32_t *)nullptr, a.n_cells);
-        return hipGetLastError();
+        return sums(bk, nbits, starts);
     };
     if (!pl.mid) {
         s.kin = a.keys_b;

@@ -1,5 +1,6 @@
 // Prints how the sort by cell plans calls, for the host-side test of its limits: first the limits, then one line per
-// (n, key bits) with the tile size, the digits, the scratch of the call and the scratch a handle of that size holds.
+// (n, key bits) with the tile size, the digits, the scratch of the call, the scratch a handle of that size
+// holds, and the tiles of a run of the digit sums.
 #include <cstdio>
 
 #include "../paper_2110_11398_amd/csrc/sort_plan.h"
@@ -14,8 +15,8 @@ int main() {
         for (int bits = 5; bits <= 31; bits++) {
             const SortPlan p = sort_plan(n, bits);
             const SortScratch s = sort_scratch(n, p);
-            printf("%lld %d %d %d %d %d %zu %zu %zu %zu\n", (long long)n, bits, tile_size(n), p.part, p.mid, p.last,
-                   s.dbase, s.rows, s.total, sort_temp_bytes(n, bits));
+            printf("%lld %d %d %d %d %d %zu %zu %zu %zu %d\n", (long long)n, bits, tile_size(n), p.part, p.mid, p.last,
+                   s.dbase, s.rows, s.total, sort_temp_bytes(n, bits), 1 << run_shift(n));
         }
     return 0;
 }

@@ -159,6 +159,31 @@ def test_build_cells_at_the_edges_of_the_sort_plan(nf, n, K):
 
 
 
+@pytest.mark.parametrize("n,K", [(262145, 9), (524289, 5), (524289, 6), (524289, 7), (128 * 4096, 30), (128 * 4096 + 1, 30),
+                                 (256 * 4096, 64), (256 * 4096 + 1, 64), (270000, 101), (2500000, 5), (1200000, 162)])
+@pytest.mark.parametrize("where", ["one cell", "one slab", "two cells"])
+def test_build_cells_crowded_into_few_buckets(nf, n, K, where):
+    """Particles that crowd into one or two buckets, whose tiles make more than one run of the digit sums: 128 and 129
+    tiles, 256 and 257, a middle digit, and cell indices of up to eight bits, which take one digit."""
+    rng = np.random.default_rng(n + K)
+    pos = 0.1 + 0.8 * rng.random((n, 3))
+    pos[:, 0] = (1 + pos[:, 0]) / K
+    if where != "one slab":
+        pos[:, 1:] = (np.array([K - 1, 2]) + pos[:, 1:]) / K
+    if where == "two cells":
+        pos[::3, 0] += (K - 2) / K
+    pos = pos.astype(np.float32)
+    boxes = [(n, 1.0, K)]
+    perm, start, spos, keys = expected_cells(pos, boxes)
+    c = nf.build_cells(torch.from_numpy(pos).cuda(), boxes, 2)
+    nf.sync()
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_PERM).cpu().numpy(), perm)
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_CELL_START).cpu().numpy(), start)
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_CELL_KEY).cpu().numpy(), keys)
+    assert np.array_equal(c.copy(nf.abacus_nf.ARRAY_SPOS).cpu().numpy(), spos)
+    c.free()
+
+
 def test_build_cells_with_more_than_2_to_the_30_cells(nf):
     """The longest keys (31 bits) in a call of the largest tiles: nine leading bits and two digits more."""
     K, n = 1025, 600001

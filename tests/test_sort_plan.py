@@ -24,7 +24,7 @@ def plans(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     out = subprocess.run([exe], capture_output=True, text=True, check=True).stdout.splitlines()
-    names = ("n", "bits", "tile", "part", "mid", "last", "dbase", "rows", "total", "handle")
+    names = ("n", "bits", "tile", "part", "mid", "last", "dbase", "rows", "total", "handle", "run")
     return tuple(map(int, out[0].split())), [dict(zip(names, map(int, line.split()))) for line in out[1:]]
 
 
@@ -59,6 +59,20 @@ def test_every_array_lies_inside_the_scratch(plans):
                 need += 2 * 4 * n + 255
             assert r["total"] - r["rows"] >= need, r
         assert r["handle"] >= r["total"], r
+
+
+def test_no_workgroup_walks_all_tiles_of_a_large_call(plans):
+    """The digit sums of a bucket that holds every particle: a run of tiles, then the runs, each a few hundred rows."""
+    _, rows = plans
+    for r in rows:
+        tiles, run = -(-r["n"] // r["tile"]), r["run"]
+        runs = -(-tiles // run)
+        assert run >= 128 and runs <= 2 * run, r
+        assert run == 128 or tiles > run * run // 2, r
+        digit, nb = max(r["mid"], r["last"]), 1 << r["part"]
+        assert r["rows"] - r["dbase"] >= 4 * ((tiles // run + nb) << digit), r
+        # few cells: one digit, however many particles
+        assert r["bits"] > 8 or (r["part"], r["mid"]) == (0, 0), r
 
 
 def test_a_handle_has_room_for_every_smaller_call(plans):
