@@ -571,12 +571,12 @@ __device__ inline double wave_max_f64(double v) {
 // raised wave priority: once one wave has started, the others reach theirs before plain work goes on, and all
 // come out in step (33 clocks a pair in the same loop).  Clustered box of 256^3 particles, K = 64, compensated
 // sums: 112.9 -> 104.0 ms at two sinks per lane and two sources a step, 120.1 -> 99.9 at four sinks.
-template <int KIND, int MODE, int S, int U, bool KDE>
+template <int KIND, int MODE, int S, int U, bool KDE, int PAIRS>
 __device__ __forceinline__ void accumulate(const float4 (&p)[U], const float (&xi)[S], const float (&yi)[S],
                                            const float (&zi)[S], float c0, float c1, float c2, float e2,
                                            float ib2, float kc, float (&ax)[S], float (&ay)[S], float (&az)[S],
                                            double (&dxs)[S], double (&dys)[S], double (&dzs)[S], float (&rh)[S]) {
-    constexpr int G = S * U <= kGroupPairs ? U : kGroupPairs / S;   // sources of a group
+    constexpr int G = S * U <= PAIRS ? U : PAIRS / S;   // sources of a group
 #pragma unroll
     for (int u0 = 0; u0 < U; u0 += G) {
         float dx[G][S], dy[G][S], dz[G][S], r2[G][S], ri[G][S], gg[G][S];
@@ -672,6 +672,9 @@ template <int KIND, int MODE, int S, int U, int OCC, bool KDE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OCC > 0 ? OCC : 4, OCC > 0 ? OCC : 8)))
 void k_forces(KArgs a) {
     constexpr int NC = KDE ? 4 : 3;  // reduced components per sink: acceleration (+ density)
+    // 64 or 80 registers a lane hold neither eight pairs of a group nor, at 64, a chunk under way during the sums
+    constexpr int kGroup = OCC > 0 ? kGroupPairs / 2 : kGroupPairs;
+    constexpr bool kAhead = OCC < 8;
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = sgpr(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -877,7 +880,7 @@ void k_forces(KArgs a) {
                     stage[q] = make_float4(kFar, kFar, kFar, 0.f);
                 }
             }
-            if (f + n < j1) fetch(f + n, min(nmax, j1 - f - n));
+            if (kAhead && f + n < j1) fetch(f + n, min(nmax, j1 - f - n));
             wave_lds_sync();
 
             if constexpr (MODE == ABACUS_NF_SUM_COMP32) {
@@ -893,7 +896,7 @@ void k_forces(KArgs a) {
 #pragma unroll
                     for (int u = 0; u < U; u++) p[u] = sp[u];
                     sp += U;
-                    accumulate<KIND, MODE, S, U, KDE>(p, xi, yi, zi, c0, c1, c2, e2, ib2, kc, ax, ay, az, dxs, dys,
+                    accumulate<KIND, MODE, S, U, KDE, kGroup>(p, xi, yi, zi, c0, c1, c2, e2, ib2, kc, ax, ay, az, dxs, dys,
                                                       dzs, rh);
                 }
             } else {
@@ -903,7 +906,7 @@ void k_forces(KArgs a) {
 #pragma unroll
                     for (int u = 0; u < U; u++) p[u] = sp[u * L];
                     sp += step;
-                    accumulate<KIND, MODE, S, U, KDE>(p, xi, yi, zi, c0, c1, c2, e2, ib2, kc, ax, ay, az, dxs, dys,
+                    accumulate<KIND, MODE, S, U, KDE, kGroup>(p, xi, yi, zi, c0, c1, c2, e2, ib2, kc, ax, ay, az, dxs, dys,
                                                       dzs, rh);
                 }
             }
@@ -928,6 +931,7 @@ void k_forces(KArgs a) {
                 }
                 if constexpr (kLowLds) store_low(low, lx, ly, lz);
             }
+            if (!kAhead && f + n < j1) fetch(f + n, min(nmax, j1 - f - n));
             wave_lds_sync();
             f += n;
         }

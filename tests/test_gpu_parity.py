@@ -420,6 +420,19 @@ def test_lattice_has_zero_force(nf, K, off, kind):
             c.free()
 
 
+@pytest.mark.parametrize("occupancy", [6, 8])
+@pytest.mark.parametrize("S,U", [(2, 4), (4, 1), (4, 2), (4, 4)])
+def test_register_budgets_of_large_tiles(nf, cut_cells, S, U, occupancy):
+    """Register budgets of six and eight waves: smaller groups of pairs, and no chunk fetched ahead at eight."""
+    pos, K, eps, ref, pairs, mag = cut_cells
+    for mode in (0, 1, 2):
+        for kw in ({}, dict(chunk=256, part_sources=1024, max_lanes=8)):
+            a, c = run(nf, pos, [(len(pos), 1.0, K)], [eps], [1.0 / len(pos)], SPLINE, mode,
+                       tuning=dict(sinks_per_lane=S, unroll=U, occupancy=occupancy, **kw))
+            check(a, ref, mag, f"S={S} U={U} occupancy={occupancy} mode={mode} {kw}")
+            c.free()
+
+
 def test_forced_source_splitting_matches(nf):
     """A heavy cell with its source list split into many parts (deterministic FP64 combination)."""
     rng = np.random.default_rng(7)
