@@ -345,7 +345,8 @@ int abacus_nf_copy_cells(abacus_nf_cells cells, abacus_nf_array which, void *dst
  * "library default".  The autotuner (abacus_nf_autotune) fills it.
  */
 typedef struct {
-    int32_t sinks_per_lane;  /* i-tile per lane: 1, 2 or 4 (0: 4, and 2 for FP64 sums)       */
+    int32_t sinks_per_lane;  /* i-tile per lane: 1, 2 or 4 (0: 4; 2 for FP64 sums and where
+                                max_lanes < 16)                                              */
     int32_t chunk;           /* j-tile: sources staged per LDS chunk (multiple of 64,
                                 64*unroll <= chunk <= 512; at most 256 are staged at a time) */
     int32_t unroll;          /* sources in flight per lane: 1, 2 or 4                        */
@@ -363,7 +364,7 @@ typedef struct {
 /* Set the tuning used by later forces calls on this handle (NULL = defaults). */
 int abacus_nf_set_tuning(abacus_nf_cells cells, const abacus_nf_tuning *tuning);
 
-/* Read the tuning in effect (defaults resolved; default sinks per lane as they are for FP32 and compensated sums). */
+/* Read the tuning in effect (defaults resolved; 4 for default sinks per lane). */
 int abacus_nf_get_tuning(abacus_nf_cells cells, abacus_nf_tuning *tuning);
 
 /*

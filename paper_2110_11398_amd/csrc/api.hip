@@ -209,17 +209,18 @@ int key_bits(int64_t n_cells) {
     return b;
 }
 
-// Sinks per lane of FP64 sums by default: four would spill 57 registers a lane with the spline, two none (spline,
+// Sinks per lane by default of FP64 sums: four would spill 57 registers a lane with the spline, two none (spline,
 // clustered, 8.4 million / 1.05 million particles: 29.8 / 2.33 ms at two, 30.4 / 2.48 at four; with the density 33.4 /
-// 2.60 and 35.7 / 2.96; 1.05 million in sparse cells 1.17 and 1.60).
-constexpr int kSinksFp64 = 2;
+// 2.60 and 35.7 / 2.96; 1.05 million in sparse cells 1.17 and 1.60).  And where few lanes may share a sink, as four
+// sinks a lane then leave lanes without any (1.05 million clustered, compensated sums, ms at two and four sinks: one
+// lane a sink 4.80 / 8.03, two 2.93 / 4.56, four 2.04 / 2.81, eight 1.71 / 1.99, sixteen 1.75 / 1.67).
+constexpr int kSinksFew = 2, kFewLanes = 16;
 
 abacus_nf_tuning default_tuning() {
     abacus_nf_tuning t;
     memset(&t, 0, sizeof(t));
     // four sinks per lane and two sources a step: eight reciprocal square roots issued together (clustered box of
-    // 256^3 particles: 99.9 ms; two sinks and two or four sources 104, four sinks and one source 104); FP64 sums
-    // take kSinksFp64
+    // 256^3 particles: 99.9 ms; two sinks and two or four sources 104, four sinks and one source 104)
     t.sinks_per_lane = 4;
     t.chunk = 256;
     t.unroll = 2;
@@ -463,7 +464,7 @@ static int ensure_work_buffers(abacus_nf_cells_s *h) {
 // The handle's tuning, as it is for a summation mode.
 static abacus_nf_tuning tuning_of(const abacus_nf_cells_s *h, abacus_nf_sum mode) {
     abacus_nf_tuning t = h->tune;
-    if (h->default_sinks && mode == ABACUS_NF_SUM_FP64) t.sinks_per_lane = kSinksFp64;
+    if (h->default_sinks && (mode == ABACUS_NF_SUM_FP64 || t.max_lanes < kFewLanes)) t.sinks_per_lane = kSinksFew;
     return t;
 }
 

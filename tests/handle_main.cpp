@@ -168,13 +168,14 @@ int main() {
         printf(" again %d null=%d\n", forces(h), (int)null_pointer);
     }
     printf("want %lld least %lld\n", (long long)want.slots, (long long)least.slots);
-    // sinks per lane of the summation modes: by default, set, set with others, and by default again
-    for (int set : {0, 4, 1, -1}) {
+    // sinks per lane of the summation modes: by default, set, by default again, and with few lanes
+    for (int set : {0, 4, 1, -1, -8}) {
         abacus_nf_tuning t;
         abacus_nf_get_tuning(h, &t);
         t.item_capacity = 0;
         t.sinks_per_lane = set > 0 ? set : 0;
-        abacus_nf_set_tuning(h, set < 0 ? nullptr : &t);
+        if (set == -8) t.max_lanes = 8;
+        abacus_nf_set_tuning(h, set == -1 ? nullptr : &t);
         printf("sinks");
         for (abacus_nf_sum mode : {ABACUS_NF_SUM_FP32, ABACUS_NF_SUM_COMP32, ABACUS_NF_SUM_FP64}) {
             abacus_nf_forces(h, one, ABACUS_NF_SPLINE, one, mode, fake, nullptr);

@@ -50,5 +50,6 @@ def test_the_force_pass_takes_the_least_lists_where_memory_is_short(lines):
     assert lines[8] == f"build {OK} forces {ENOMEM} again {OK} null=0"
 
 
-def test_fp64_sums_take_two_sinks_per_lane_unless_set(lines):
-    assert lines[10:] == ["sinks 4 4 2 get 4", "sinks 4 4 4 get 4", "sinks 1 1 1 get 1", "sinks 4 4 2 get 4"]
+def test_fp64_sums_and_few_lanes_take_two_sinks_per_lane_unless_set(lines):
+    assert lines[10:14] == ["sinks 4 4 2 get 4", "sinks 4 4 4 get 4", "sinks 1 1 1 get 1", "sinks 4 4 2 get 4"]
+    assert lines[14:] == ["sinks 2 2 2 get 4"]
