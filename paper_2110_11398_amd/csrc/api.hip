@@ -54,7 +54,8 @@ struct abacus_nf_cells_s {
 
     // force work buffers
     int64_t wcap_cells = -1, wcap_items = -1, wcap_partials = -1, wcap_boxes = -1;
-    int64_t want_slots = -1, want_items = -1;   // what the lists were sized for (they hold less where memory is short)
+    // what the lists were sized for (they hold less where memory is short), and the item capacity they were forced to
+    int64_t want_slots = -1, want_items = -1, forced_items = -1;
     ForceBox *d_fbox = nullptr;
     WorkState *ws = nullptr;
     WorkBox *wb = nullptr;
@@ -200,7 +201,7 @@ void free_work_buffers(abacus_nf_cells_s *h) {
     h->cell_amax = nullptr;
     h->amax_valid = false;
     h->wcap_cells = h->wcap_items = h->wcap_partials = h->wcap_boxes = -1;
-    h->want_slots = h->want_items = -1;
+    h->want_slots = h->want_items = h->forced_items = -1;
 }
 
 int key_bits(int64_t n_cells) {
@@ -431,8 +432,9 @@ static int check_force_args(abacus_nf_cells h, const double *eps, abacus_nf_kind
 static int ensure_work_buffers(abacus_nf_cells_s *h) {
     const int64_t n = std::max<int64_t>(h->n_total, 1), nc = std::max<int64_t>(h->n_cells, 1);
     const ListRoom want = list_room(n, nc, h->n_boxes);
-    const int64_t forced = h->tune.item_capacity, want_items = forced > 0 ? forced : want.items;
-    if (h->wcap_cells >= nc && h->wcap_boxes >= h->n_boxes && h->want_slots >= want.slots && h->want_items == want_items)
+    const int64_t forced = h->tune.item_capacity;
+    if (h->wcap_cells >= nc && h->wcap_boxes >= h->n_boxes && h->want_slots >= want.slots &&
+        h->want_items >= want.items && h->forced_items == forced)
         return ABACUS_NF_OK;
     for (const ListRoom &r : {want, least_room(n, nc)}) {   // the least lists where memory is short
         free_work_buffers(h);
@@ -453,7 +455,8 @@ static int ensure_work_buffers(abacus_nf_cells_s *h) {
             h->wcap_partials = r.slots;
             h->wcap_boxes = h->n_boxes;
             h->want_slots = want.slots;
-            h->want_items = want_items;
+            h->want_items = want.items;
+            h->forced_items = forced;
             return ABACUS_NF_OK;
         }
     }

@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <vector>
 
 #include "../paper_2110_11398_amd/csrc/nf_internal.h"
 
@@ -11,12 +12,14 @@ static size_t budget = 0, used = 0;
 static std::map<char *, size_t> live;
 static char *next_address = (char *)0x100000;
 static bool null_pointer = false;
+static int allocations = 0;
 static anf::ForcesArgs last_forces;
 
 extern "C" {
 hipError_t hipMalloc(void **p, size_t bytes) {
     if (used + bytes > budget) return hipErrorOutOfMemory;
     used += bytes;
+    allocations++;
     live[next_address] = bytes;
     *p = next_address;
     next_address += (bytes + 4095) / 4096 * 4096;
@@ -184,6 +187,26 @@ int main() {
         abacus_nf_get_tuning(h, &t);
         printf(" get %d\n", t.sinks_per_lane);
     }
+    // smaller calls on the handle of a batch: fewer boxes of the same totals, fewer particles and cells
+    abacus_nf_set_tuning(h, nullptr);
+    for (int round = 0; round < 2; round++)
+        for (int n_boxes : {8, 4, 2, 1, 3}) {
+            std::vector<abacus_nf_box> b(n_boxes);
+            std::vector<double> v(n_boxes, 0.01);
+            const int64_t n = 840000 / n_boxes, odd = round ? 17 : 0;
+            const int K = n_boxes == 8 ? 40 : n_boxes == 3 ? 20 : 50;
+            for (int i = 0; i < n_boxes; i++) {
+                b[i] = abacus_nf_box{};
+                b[i].offset = i * (n - odd);
+                b[i].n = n - odd;
+                b[i].box = 1.0;
+                b[i].K = K;
+            }
+            allocations = 0;
+            int rc = abacus_nf_build_cells(fake, n_boxes * (n - odd), b.data(), n_boxes, 2, nullptr, &h);
+            if (rc == 0) rc = abacus_nf_forces(h, v.data(), ABACUS_NF_SPLINE, v.data(), ABACUS_NF_SUM_FP32, fake, nullptr);
+            printf("boxes %d rc %d allocations %d\n", n_boxes, rc, allocations);
+        }
     abacus_nf_free_cells(h);
     return 0;
 }

@@ -52,4 +52,10 @@ def test_the_force_pass_takes_the_least_lists_where_memory_is_short(lines):
 
 def test_fp64_sums_and_few_lanes_take_two_sinks_per_lane_unless_set(lines):
     assert lines[10:14] == ["sinks 4 4 2 get 4", "sinks 4 4 4 get 4", "sinks 1 1 1 get 1", "sinks 4 4 2 get 4"]
-    assert lines[14:] == ["sinks 2 2 2 get 4"]
+    assert lines[14] == "sinks 2 2 2 get 4"
+
+
+def test_smaller_calls_on_a_handle_allocate_nothing(lines):
+    got = lines[15:]
+    assert got[0].startswith(f"boxes 8 rc {OK} ")
+    assert got[1:] == [f"boxes {b} rc {OK} allocations 0" for b in (4, 2, 1, 3, 8, 4, 2, 1, 3)]
