@@ -103,8 +103,10 @@ typedef struct abacus_nf_cells_s *abacus_nf_cells;
  *
  * Enqueues: binning, a stable sort of particles by cell (input order within a
  * cell), the cell offsets, and the cell-relative FP32 coordinates.
- * Errors: EINVAL for bad arguments; ENOMEM; EDEVICE.  Non-finite positions
- * are reported later by abacus_nf_sync as ENONFINITE.
+ * Errors: EINVAL for bad arguments; ENOMEM (a handle that had to grow then holds
+ * no cells, and every call on it returns ESTATE until a build succeeds);
+ * EDEVICE.  Non-finite positions are reported later by abacus_nf_sync as
+ * ENONFINITE.
  */
 int abacus_nf_build_cells(const float *pos, int64_t n_total, const abacus_nf_box *boxes,
                           int32_t n_boxes, int32_t R, void *hip_stream, abacus_nf_cells *cells);
@@ -126,6 +128,10 @@ int abacus_nf_build_cells(const float *pos, int64_t n_total, const abacus_nf_box
  * Allocates nothing when the handle already holds the work buffers of an
  * earlier forces call of the same batch (so it may be captured in a HIP
  * graph after one eager call).
+ * The handle's work buffers take at most 64 bytes a particle or 4.3 GB,
+ * whichever is more, for partial sums, and a few bytes a particle and 28 a cell
+ * for the work list; 32 bytes a particle where that much memory is not free.
+ *
  * Errors: EINVAL, ESTATE (handle not built), ENOMEM, EDEVICE; ECAPACITY is
  * reported by abacus_nf_sync if a device work list overflows.
  */

@@ -164,12 +164,11 @@ int tune(abacus_nf_cells h, const double *eps, abacus_nf_kind kind, const double
             }
     // stage 2: j-tile (LDS chunk) and lane sharing around the best of stage 1
     const abacus_nf_tuning s1 = best_t;
-    for (int chunk : {128})
-        if (rc == ABACUS_NF_OK) {
-            abacus_nf_tuning t = s1;
-            t.chunk = chunk;
-            rc = trial(t);
-        }
+    if (rc == ABACUS_NF_OK) {
+        abacus_nf_tuning t = s1;
+        t.chunk = 128;
+        rc = trial(t);
+    }
     const abacus_nf_tuning s2 = best_t;
     for (int ml : {4, 16})
         if (rc == ABACUS_NF_OK) {

@@ -8,8 +8,10 @@
 // launch drains it:
 //
 //   k_wl_cells    per cell: occupancy n_c, near-field source count; per box: pair and work totals
-//   k_wl_plan     the source-part length of every box
-//   k_wl_count    per cell: tiles x parts, partial slots, cost class (histogram over classes)
+//   k_wl_plan     the source-part length of every box, and up to which length a cell is not split over items
+//   k_wl_bins,    where the lists are short: what splitting the cells of every length takes, and which stay whole
+//   k_wl_fit      so that the rest fits
+//   k_wl_count    per cell: items, partial slots, cost class (histogram over classes)
 //   k_wl_emit     class offsets (heaviest items first), capacity checks, items in class order
 //   k_forces      persistent waves pop items: sink tile in VGPRs, sources staged
 //                 through the wave's LDS region with the periodic cell offset
@@ -696,7 +698,9 @@ void k_forces(KArgs a) {
     // (32768 particles: 0.48 ms of 0.91).
     int x = blockIdx.x % kQueues;
     int jnext = (int)(blockIdx.x / kQueues) * kWaves + wave, jleft = 1;
-    int k = n_items, part = 0, parts_left = 0;   // parts of the last item that are still to be done
+    // An item of a whole source list is gone through again for each of its parts.  (A loop over the parts inside saves
+    // their set-up but spills twelve registers more of the default kernels, for what it keeps from part to part.)
+    int k = n_items, part = 0, parts_left = 0;
     for (;;) {
         if (parts_left == 0) k = n_items;
         while (parts_left == 0) {
@@ -1037,7 +1041,7 @@ void k_forces(KArgs a) {
     }
 }
 
-// Sinks whose source list was split: add the parts in order and write the result.
+// Sinks whose source list was split over items: add the parts in order and write the result.
 template <int MODE, int NC>
 __global__ __launch_bounds__(256) void k_finalize(const WorkState *__restrict__ ws, int64_t partial_capacity,
                                                   const int32_t *__restrict__ keys, const int32_t *__restrict__ cs,

@@ -30,7 +30,8 @@ struct ForceBox {
 };
 
 // One unit of work of the persistent force kernel: a tile of sinks of one
-// cell against one part of that cell's near-field source list.
+// cell against one part of that cell's near-field source list, or against all
+// parts in turn where the list stays whole.
 struct Item {
     int32_t cell, tile, part, box;
 };
