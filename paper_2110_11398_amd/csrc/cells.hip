@@ -11,8 +11,7 @@
 //   k_seg_scatter  as partition: stable scatter by the leading digit (up to 8 bits) of coordinates, input index and
 //                  cell; every later step then works inside one bucket, whose few MB stay in cache
 //   k_seg_hist,    per bucket: digit counts of every tile, their exclusive sums over runs of tiles, and the first slots
-//   k_seg_sums,    of the digits in every run
-//   k_seg_base
+//   k_seg_sums     of the digits in every run (k_seg_base where one bucket has several runs)
 //   k_seg_scatter  stable scatter inside the buckets; the last one writes the sorted keys, the permutation and
 //                  the cell-relative coordinates in cell widths, FP64 -> FP32
 //
@@ -227,6 +226,7 @@ __global__ __launch_bounds__(kMaxBuckets) void k_buckets(const uint32_t *__restr
     o->start[b] = lo;
     o->tile[b] = tiles - t;
     o->run[b] = runs - r;
+    o->done[b] = 0;
     if (b == kMaxBuckets - 1) {
         o->start[kMaxBuckets] = (uint32_t)n;
         o->tile[kMaxBuckets] = tiles;
@@ -345,39 +345,14 @@ __device__ inline uint4 digit_starts(const uint4 &sum, int b, uint32_t start, in
     return o;
 }
 
-// One workgroup per run of tiles: their rows of digit counts become exclusive sums over the run, four digits to a
-// thread, and dbase, per run, the digits' totals.  Where every bucket is one run (`single`) dbase gets the first slots
-// at once.
-__global__ __launch_bounds__(kSegScanThreads) void k_seg_sums(uint32_t *__restrict__ rows, uint32_t *__restrict__ dbase,
-                                                              const Buckets *__restrict__ bk, int nb, int64_t n,
-                                                              int ntiles, int run_shift, int bits, int single,
-                                                              int32_t *__restrict__ cell_start, int64_t n_cells) {
-    const int Q = 1 << (bits - 2), tid = threadIdx.x, g = blockIdx.x;   // Q groups of four digits
-    int b = 0, t0 = g << run_shift, end = ntiles;
-    if (bk) {
-        if (g >= bk->run[kMaxBuckets]) return;
-        b = single ? g : bucket_at<kSegScanThreads>(bk->run, nb, g);
-        t0 = bk->tile[b] + ((g - bk->run[b]) << run_shift);
-        end = bk->tile[b + 1];
-    }
-    const int t1 = end - t0 < (1 << run_shift) ? end : t0 + (1 << run_shift);
-    uint4 sum = make_uint4(0, 0, 0, 0);
-    if (tid < Q) sum = scan_rows((uint4 *)rows + (int64_t)t0 * Q + tid, t0, t1, Q);
-    if (single) sum = digit_starts(sum, b, bk ? bk->start[b] : 0u, Q, n, cell_start, n_cells);
-    if (tid < Q) ((uint4 *)dbase)[(int64_t)g * Q + tid] = sum;
-}
-
-// One workgroup per bucket: the totals of its runs become the first slots of the digits in each run.
-__global__ __launch_bounds__(kSegScanThreads) void k_seg_base(uint32_t *__restrict__ dbase,
-                                                              const Buckets *__restrict__ bk, int64_t n, int nruns,
-                                                              int bits, int32_t *__restrict__ cell_start,
-                                                              int64_t n_cells) {
-    const int Q = 1 << (bits - 2), tid = threadIdx.x, b = blockIdx.x;
-    const int r0 = bk ? bk->run[b] : 0, r1 = bk ? bk->run[b + 1] : nruns;
+// The totals of runs [r0, r1) of bucket b become the first slots of the digits in each run.  The whole workgroup.
+__device__ inline void run_bases(uint32_t *dbase, int r0, int r1, int Q, int b, uint32_t start, int64_t n,
+                                 int32_t *__restrict__ cell_start, int64_t n_cells) {
+    const int tid = threadIdx.x;
     uint4 *col = (uint4 *)dbase + (int64_t)r0 * Q + tid;
     uint4 sum = make_uint4(0, 0, 0, 0);
     if (tid < Q) sum = scan_rows(col, r0, r1, Q);
-    const uint4 first = digit_starts(sum, b, bk ? bk->start[b] : 0u, Q, n, cell_start, n_cells);
+    const uint4 first = digit_starts(sum, b, start, Q, n, cell_start, n_cells);
     if (tid < Q)
 #pragma unroll 8
         for (int r = r0; r < r1; r++, col += Q) {
@@ -385,6 +360,51 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_base(uint32_t *__restri
             add4(v, first);
             *col = v;
         }
+}
+
+// One workgroup per run of tiles: their rows of digit counts become exclusive sums over the run, four digits to a
+// thread, and dbase, per run, the digits' totals; then the first slots, by the run itself where it is its bucket's only
+// one (`single`: every one is), else by the run of the bucket that ends last.  (A kernel of its own for the latter cost
+// every call of more than 128 tiles 5 us a digit.)  With one bucket of several runs k_seg_base does it.
+__global__ __launch_bounds__(kSegScanThreads) void k_seg_sums(uint32_t *rows, uint32_t *dbase, Buckets *bk, int nb, int64_t n,
+                                                              int ntiles, int run_shift, int bits, int single,
+                                                              int32_t *__restrict__ cell_start, int64_t n_cells) {
+    __shared__ int last;
+    const int Q = 1 << (bits - 2), tid = threadIdx.x, g = blockIdx.x;   // Q groups of four digits
+    int b = 0, t0 = g << run_shift, end = ntiles, r0 = 0, r1 = single ? 1 : 2;
+    uint32_t start = 0;
+    if (bk) {
+        if (g >= bk->run[kMaxBuckets]) return;
+        b = single ? g : bucket_at<kSegScanThreads>(bk->run, nb, g);
+        r0 = bk->run[b];
+        r1 = bk->run[b + 1];
+        t0 = bk->tile[b] + ((g - r0) << run_shift);
+        end = bk->tile[b + 1];
+        start = bk->start[b];
+    }
+    const int t1 = end - t0 < (1 << run_shift) ? end : t0 + (1 << run_shift);
+    uint4 sum = make_uint4(0, 0, 0, 0);
+    if (tid < Q) sum = scan_rows((uint4 *)rows + (int64_t)t0 * Q + tid, t0, t1, Q);
+    if (r1 - r0 == 1) sum = digit_starts(sum, b, start, Q, n, cell_start, n_cells);
+    if (tid < Q) ((uint4 *)dbase)[(int64_t)g * Q + tid] = sum;
+    if (!bk || r1 - r0 == 1) return;
+    // the totals of every run are in memory before it is counted, and read after the last count
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) {
+        last = atomicAdd(&bk->done[b], 1) == r1 - r0 - 1;
+        if (last) bk->done[b] = 0;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    run_bases(dbase, r0, r1, Q, b, start, n, cell_start, n_cells);
+}
+
+// The first slots of one bucket of several runs.
+__global__ __launch_bounds__(kSegScanThreads) void k_seg_base(uint32_t *dbase, int64_t n, int nruns, int bits,
+                                                              int32_t *__restrict__ cell_start, int64_t n_cells) {
+    run_bases(dbase, 0, nruns, 1 << (bits - 2), 0, 0u, n, cell_start, n_cells);
 }
 
 // What a scatter reads and writes.
@@ -676,16 +696,15 @@ hipError_t sort_impl(const SortArgs &a, const SortPlan &pl, int bits, int32_t **
     *have_starts = pl.mid == 0;
     const int nb = 1 << pl.part, shift_runs = s.run_shift;
     // first slots of a digit of nbits bits from the tiles' counts
-    auto sums = [&](const Buckets *buckets, int nbits, bool starts) {
+    auto sums = [&](Buckets *buckets, int nbits, bool starts) {
         const int runs = buckets ? (ntiles >> shift_runs) + nb : (int)((ntiles + ((int64_t)1 << shift_runs) - 1) >> shift_runs);
         const bool single = ntiles <= (1 << shift_runs);
         int32_t *cell_start = starts ? a.cell_start : nullptr;
         hipLaunchKernelGGL(k_seg_sums, dim3(runs), dim3(kSegScanThreads), 0, st, rows, dbase, buckets, nb, n, ntiles,
                            shift_runs, nbits, (int)single, cell_start, a.n_cells);
         hipError_t r = hipGetLastError();
-        if (r != hipSuccess || single) return r;
-        hipLaunchKernelGGL(k_seg_base, dim3(buckets ? nb : 1), dim3(kSegScanThreads), 0, st, dbase, buckets, n, runs, nbits,
-                           cell_start, a.n_cells);
+        if (r != hipSuccess || single || buckets) return r;
+        hipLaunchKernelGGL(k_seg_base, dim3(1), dim3(kSegScanThreads), 0, st, dbase, n, runs, nbits, cell_start, a.n_cells);
         return hipGetLastError();
     };
     if (!pl.part) {

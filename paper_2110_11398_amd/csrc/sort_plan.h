@@ -21,6 +21,7 @@ struct Buckets {
     uint32_t start[kMaxBuckets + 1];
     int32_t tile[kMaxBuckets + 1];
     int32_t run[kMaxBuckets + 1];
+    int32_t done[kMaxBuckets];   // runs of the bucket summed so far, 0 between digits
 };
 
 // Tiles: 4096 elements in large calls, four to a thread, so that two workgroups of sixteen waves fit a CU (build of
@@ -35,8 +36,7 @@ inline int64_t tile_number(int64_t n) { return (n + tile_size(n) - 1) / tile_siz
 
 // Log2 of the tiles in a run: 128, and more where the runs of one bucket that holds all tiles would be more than twice
 // that.  Particles that crowd into one bucket (a zoomed box, one heavy cell) would leave its sums to one workgroup: 0.35
-// to 1.2 ms a digit for 33.5 million particles, 25 to 50 us in runs (whose second kernel costs other calls of more than
-// 128 tiles 3 us a digit).
+// to 1.2 ms a digit for 33.5 million particles, 25 to 50 us in runs.
 inline int run_shift(int64_t n) {
     int s = 7;
     while (((int64_t)2 << (2 * s)) < tile_number(n)) s++;
