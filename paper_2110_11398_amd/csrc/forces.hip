@@ -59,6 +59,8 @@ __device__ inline void clear_work(WorkState *ws, WorkBox *wb, int first, int cou
         ws->partial_slots = 0;
         ws->n_items = 0;
         ws->overflow = 0;
+        ws->pairs = 0;
+        ws->whole_bin = -1;
         ws->whole_slots = ws->whole_items = 0;
     }
     // the first slots of every queue belong to the waves that start on it
@@ -261,6 +263,12 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
     }
 }
 
+// Source iterations per lane of a wave's share of `pairs` pairs, at most part_sources.
+__device__ inline int fill_length(unsigned long long pairs, int S, int part_sources) {
+    const unsigned long long fill = pairs / ((unsigned long long)(64 * S) * kFillItems);
+    return fill > (unsigned long long)part_sources ? part_sources : (int)fill;
+}
+
 // Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
 // at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
 // leaves the rest of the chip idle until it ends.  The length is at most the tuning's part_sources and at least
@@ -274,15 +282,15 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
 __global__ __launch_bounds__(256) void k_wl_plan(WorkState *__restrict__ ws, WorkBox *__restrict__ wb,
                                                  const BoxDev *__restrict__ boxes, int n_boxes, int S,
                                                  int part_sources) {
-    __shared__ unsigned long long pairs;
+    __shared__ unsigned long long pairs;   // of this workgroup's boxes
     if (threadIdx.x == 0) pairs = 0;
     __syncthreads();
-    const unsigned long long share = (unsigned long long)(64 * S) * kFillItems;
-    auto capped = [&](unsigned long long fill) { return fill > (unsigned long long)part_sources ? part_sources : (long long)fill; };
-    for (int b = threadIdx.x; b < n_boxes; b += blockDim.x) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < n_boxes) {
         const WorkBox w = wb[b];
         const int64_t n = boxes[b].n, K = boxes[b].K;
-        const long long want = capped(w.pairs / share), least = least_part(w.pairs, S), it = want < least ? least : want;
+        const long long want = fill_length(w.pairs, S, part_sources), least = least_part(w.pairs, S);
+        const long long it = want < least ? least : want;
         // bounds at this length: slots <= n + slot_iters / length, items <= tiles + item_iters / length
         const double slots = (double)(w.slot_iters / it + 1), items = (double)(w.item_iters / it + 1);
         const double slot_room = (double)(box_slots(n) - n), item_room = (double)box_items(n, K * K * K) - (double)w.tiles;
@@ -294,10 +302,7 @@ __global__ __launch_bounds__(256) void k_wl_plan(WorkState *__restrict__ ws, Wor
         if (w.pairs) atomicAdd(&pairs, w.pairs);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        ws->whole_iters = (int32_t)capped(pairs / share);
-        ws->whole_bin = -1;
-    }
+    if (threadIdx.x == 0 && pairs) atomicAdd(&ws->pairs, pairs);
 }
 
 // Length bin of a cell's source list: half octaves of its source iterations.
@@ -317,7 +322,9 @@ __device__ inline int cell_split(int n, int nsrc, int S, int max_lanes, int part
 // Where the boxes' rooms add up to more than the lists hold: what splitting the cells of every length bin takes.
 __global__ __launch_bounds__(256) void k_wl_bins(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
                                                  const BoxDev *__restrict__ boxes, int n_boxes, int64_t n_cells, int S,
-                                                 int max_lanes, const WorkBox *__restrict__ wb, WorkState *ws) {
+                                                 int max_lanes, int part_sources, const WorkBox *__restrict__ wb,
+                                                 WorkState *ws) {
+    const int whole_iters = fill_length(ws->pairs, S, part_sources);
     __shared__ unsigned long long slots[kNumClasses + 1], items[kNumClasses + 1];   // the last: with every cell whole
     if (threadIdx.x <= kNumClasses) slots[threadIdx.x] = items[threadIdx.x] = 0;
     __syncthreads();
@@ -325,7 +332,7 @@ __global__ __launch_bounds__(256) void k_wl_bins(const int32_t *__restrict__ cs,
     const int n = c < n_cells ? cs[c + 1] - cs[c] : 0;
     if (n > 0) {
         const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
-        const int nsrc = cell_nsrc[c], parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, ws->whole_iters, -1);
+        const int nsrc = cell_nsrc[c], parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, whole_iters, -1);
         const unsigned long long tiles = (unsigned long long)tile_count(n, S, max_lanes);
         atomicAdd(&items[kNumClasses], tiles);
         if (parts < 0 || parts > 1) atomicAdd(&slots[kNumClasses], (unsigned long long)n);
@@ -362,8 +369,10 @@ __global__ __launch_bounds__(64) void k_wl_fit(WorkState *ws, int64_t partial_ca
 
 __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs, const int32_t *__restrict__ cell_nsrc,
                                                   const BoxDev *__restrict__ boxes, int n_boxes, int64_t n_cells, int S,
-                                                  int max_lanes, const WorkBox *__restrict__ wb, WorkState *ws,
-                                                  int32_t *__restrict__ cell_parts, int64_t *__restrict__ cell_pbase) {
+                                                  int max_lanes, int part_sources, const WorkBox *__restrict__ wb,
+                                                  WorkState *ws, int32_t *__restrict__ cell_parts,
+                                                  int64_t *__restrict__ cell_pbase) {
+    const int whole_iters = fill_length(ws->pairs, S, part_sources);
     __shared__ int32_t hist[kNumClasses];
     __shared__ unsigned long long need, base;   // partial slots of this workgroup's split cells
     if (threadIdx.x < kNumClasses) hist[threadIdx.x] = 0;
@@ -376,7 +385,7 @@ __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs
         const int n = cs[c + 1] - cs[c];
         const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
         const int nsrc = cell_nsrc[c];
-        parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, ws->whole_iters, ws->whole_bin);
+        parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, whole_iters, ws->whole_bin);
         cell_parts[c] = parts;
         const int split = parts < 0 ? 1 : parts;
         if (parts < 0 || parts > 1) local = atomicAdd(&need, (unsigned long long)split * (unsigned long long)n);
@@ -1246,17 +1255,17 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
     if (e != hipSuccess || a.n_cells <= 0) return e;
     const int S = a.tune.sinks_per_lane, ML = a.tune.max_lanes;
     const unsigned gc = grid_for(a.n_cells, 256);
-    hipLaunchKernelGGL(k_wl_plan, dim3(1), dim3(256), 0, st, a.ws, a.wb, a.boxes, a.n_boxes, S, a.tune.part_sources);
+    hipLaunchKernelGGL(k_wl_plan, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.boxes, a.n_boxes, S, a.tune.part_sources);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (a.short_room) {
         hipLaunchKernelGGL(k_wl_bins, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
-                           a.n_cells, S, ML, a.wb, a.ws);
+                           a.n_cells, S, ML, a.tune.part_sources, a.wb, a.ws);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(k_wl_fit, dim3(1), dim3(64), 0, st, a.ws, a.partial_capacity, a.item_capacity);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_wl_count, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,
-                       a.n_cells, S, ML, a.wb, a.ws, a.cell_parts, a.cell_pbase);
+                       a.n_cells, S, ML, a.tune.part_sources, a.wb, a.ws, a.cell_parts, a.cell_pbase);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // few cells have many items each: fewer cells to a workgroup then
     const int per_block = a.n_cells >= 16384 ? 256 : 16;

@@ -123,8 +123,8 @@ struct WorkState {
     unsigned long long partial_slots; // partial slots of the split cells
     int32_t n_items;                  // items emitted (0 when a list outgrew its allocation)
     int32_t overflow;                 // non-zero when a list outgrew its capacity
-    int32_t whole_iters;              // cells of up to this many source iterations are not split over items
-    int32_t whole_bin;                // nor are those of length bins up to this one, where the lists are short
+    int32_t whole_bin;                // cells of length bins up to this one are not split, where the lists are short
+    unsigned long long pairs;         // of all boxes: cells no longer than a wave's share of them are not split over items
     // where the boxes' rooms add up to more than the lists: what the lists hold with every cell whole, and what
     // splitting the cells of a length bin adds
     unsigned long long whole_slots, whole_items, bin_slots[kNumClasses], bin_items[kNumClasses];
