@@ -748,6 +748,7 @@ void k_forces(KArgs a) {
         const int cz = lin % K, cy = (lin / K) % K, cx = lin / (K * K);
         const int cs0 = a.cs[c];
         const int nc = a.cs[c + 1] - cs0;
+        const int cell_parts = a.cell_parts[c];   // needed last, fetched with the others
         const TileGeom tg = tile_at(nc, S, a.max_lanes, sgpr(it.tile));
         const int L = tg.L, G = tg.G;
         const int t0 = tg.t0;
@@ -794,7 +795,7 @@ void k_forces(KArgs a) {
 
         // parts of the source list, nsrc split into P near-equal contiguous ranges (32-bit arithmetic): the item's
         // one, or all of them in turn
-        const int split = sgpr(a.cell_parts[c]);
+        const int split = sgpr(cell_parts);
         const bool whole = split < 0;
         const int P = whole ? -split : split;
         const int pq = nsrc / P, pr = nsrc - pq * P;
