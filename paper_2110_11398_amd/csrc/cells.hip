@@ -26,6 +26,7 @@
 //
 // Every step is deterministic: particles of a cell stay in input order.
 #include <algorithm>
+#include <climits>
 #include <cstring>
 
 #include "nf_internal.h"
@@ -234,21 +235,22 @@ __global__ __launch_bounds__(kMaxBuckets) void k_buckets(const uint32_t *__restr
     }
 }
 
-// The last of the nb buckets whose first tile or run is at most g: every thread looks at a bucket or two (a binary search
-// by each thread waits for nine loads in turn).  The whole workgroup.
-template <int THREADS>
+// The last of the nb buckets whose first tile or run is at most g: the lanes of a wave look at four each at once (a
+// binary search waits for eight or nine loads in turn).
 __device__ inline int bucket_at(const int32_t *__restrict__ first, int nb, int g) {
+    const int lane = threadIdx.x & 63;
     int count = 0;
-    for (int i = 0; i < nb; i += THREADS) {
-        const int b = i + (int)threadIdx.x;
-        count += __syncthreads_count(b < nb && first[b] <= g);
+    for (int i = 0; i < nb; i += 256) {
+        int v[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) v[q] = i + 64 * q + lane < nb ? first[i + 64 * q + lane] : INT_MAX;
+#pragma unroll
+        for (int q = 0; q < 4; q++) count += __popcll(__ballot(v[q] <= g));
     }
     return count - 1;
 }
 
-// Run, first slot and number of slots of tile g (bk null: one bucket of n slots); false past the last tile.  The whole
-// workgroup.
-template <int THREADS>
+// Run, first slot and number of slots of tile g (bk null: one bucket of n slots); false past the last tile.
 __device__ inline bool seg_tile(const Buckets *__restrict__ bk, int nb, int64_t n, int tile, int run_shift, int g, int &run,
                                 int64_t &base, int &count) {
     run = g >> run_shift;
@@ -256,7 +258,7 @@ __device__ inline bool seg_tile(const Buckets *__restrict__ bk, int nb, int64_t 
     base = (int64_t)g * tile;
     if (bk) {
         if (g >= bk->tile[kMaxBuckets]) return false;
-        const int b = bucket_at<THREADS>(bk->tile, nb, g), in = g - bk->tile[b];
+        const int b = bucket_at(bk->tile, nb, g), in = g - bk->tile[b];
         run = bk->run[b] + (in >> run_shift);
         base = (int64_t)bk->start[b] + (int64_t)in * tile;
         end = bk->start[b + 1];
@@ -274,7 +276,7 @@ __global__ __launch_bounds__(THREADS) void k_seg_hist(const int32_t *__restrict_
     uint32_t *h = smem_u32;
     int run, count;
     int64_t base;
-    if (!seg_tile<THREADS>(bk, nb, n, THREADS * ITEMS, 0, blockIdx.x, run, base, count)) return;
+    if (!seg_tile(bk, nb, n, THREADS * ITEMS, 0, blockIdx.x, run, base, count)) return;
     const int D = 1 << bits, tid = threadIdx.x;
     for (int d = tid; d < D; d += THREADS) h[d] = 0;
     __syncthreads();
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_sums(uint32_t *rows, ui
     uint32_t start = 0;
     if (bk) {
         if (g >= bk->run[kMaxBuckets]) return;
-        b = single ? g : bucket_at<kSegScanThreads>(bk->run, nb, g);
+        b = single ? g : bucket_at(bk->run, nb, g);
         r0 = bk->run[b];
         r1 = bk->run[b + 1];
         t0 = bk->tile[b] + ((g - r0) << run_shift);
@@ -474,7 +476,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     int run_of, count;
     int64_t base;
-    if (!seg_tile<THREADS>(OUT == kSegPart || OUT == kSegLastPos ? nullptr : a.bk, a.nb, a.n, TILE, a.run_shift, blockIdx.x,
+    if (!seg_tile(OUT == kSegPart || OUT == kSegLastPos ? nullptr : a.bk, a.nb, a.n, TILE, a.run_shift, blockIdx.x,
                            run_of, base, count))
         return;
     for (int d = tid; d < WAVES * D / 2; d += THREADS) ((uint32_t *)wcnt)[d] = 0;

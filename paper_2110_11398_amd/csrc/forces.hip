@@ -272,8 +272,9 @@ __device__ inline int fill_length(unsigned long long pairs, int S, int part_sour
 // Length of the source parts of every box (source iterations per lane).  A box is cut so that its work gives
 // at least about kFillItems equal items: an item of a heavy cell that is longer than a wave's share of the box
 // leaves the rest of the chip idle until it ends.  The length is at most the tuning's part_sources and at least
-// kMinPart (twice that where such parts still give kFewItems items), and longer where the box's own room (box_slots, box_items) is less than its parts would take: it
-// follows from the box alone, so a box gives bit-identical forces whatever batch it is in.
+// kMinPart (twice that where such parts still give kFewItems items), and longer where the box's own room (box_slots,
+// box_items) is less than its parts would take: it follows from the box alone, so a box gives bit-identical forces
+// whatever batch it is in.
 //
 // What a batch decides is which cells are split over items at all.  A cell whose list is no longer than a wave's share
 // of the whole batch stays one item per tile, which goes through the parts in order and adds them up as k_finalize
@@ -1256,7 +1257,8 @@ hipError_t build_work_list(const ForcesArgs &a, hipStream_t st) {
     if (e != hipSuccess || a.n_cells <= 0) return e;
     const int S = a.tune.sinks_per_lane, ML = a.tune.max_lanes;
     const unsigned gc = grid_for(a.n_cells, 256);
-    hipLaunchKernelGGL(k_wl_plan, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.boxes, a.n_boxes, S, a.tune.part_sources);
+    hipLaunchKernelGGL(k_wl_plan, dim3(grid_for(a.n_boxes, 256)), dim3(256), 0, st, a.ws, a.wb, a.boxes, a.n_boxes, S,
+                       a.tune.part_sources);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (a.short_room) {
         hipLaunchKernelGGL(k_wl_bins, dim3(gc), dim3(256), 0, st, a.cell_start, a.cell_nsrc, a.boxes, a.n_boxes,

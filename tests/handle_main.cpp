@@ -189,11 +189,11 @@ int main() {
     }
     // smaller calls on the handle of a batch: fewer boxes of the same totals, fewer particles and cells
     abacus_nf_set_tuning(h, nullptr);
-    for (int round = 0; round < 2; round++)
+    for (int pass = 0; pass < 2; pass++)
         for (int n_boxes : {8, 4, 2, 1, 3}) {
             std::vector<abacus_nf_box> b(n_boxes);
             std::vector<double> v(n_boxes, 0.01);
-            const int64_t n = 840000 / n_boxes, odd = round ? 17 : 0;
+            const int64_t n = 840000 / n_boxes, odd = pass ? 17 : 0;
             const int K = n_boxes == 8 ? 40 : n_boxes == 3 ? 20 : 50;
             for (int i = 0; i < n_boxes; i++) {
                 b[i] = abacus_nf_box{};
