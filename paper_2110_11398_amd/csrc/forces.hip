@@ -145,25 +145,17 @@ __device__ inline int cell_sources(const int32_t *__restrict__ cs, const BoxDev 
     return total;
 }
 
-// Parts of the source list of a cell: as many as keep its first tile (fewest lanes per group) at about
-// part_iters source iterations per lane.
-__device__ inline int cell_part_count(int n, int nsrc, int S, int max_lanes, int part_iters) {
-    if (n <= 0) return 0;
+// Source iterations per lane of a cell's first tile (fewest lanes per group).
+__device__ inline int cell_iters(int n, int nsrc, int S, int max_lanes) {
     const int L0 = tile_at(n, S, max_lanes, 0).L;
-    const int64_t iters = ((int64_t)nsrc + L0 - 1) / L0;
-    int64_t parts = (iters + part_iters - 1) / part_iters;
-    if (parts < 1) parts = 1;
-    if (parts > nsrc) parts = nsrc > 0 ? nsrc : 1;
-    return (int)parts;
+    return (nsrc + L0 - 1) / L0;
 }
 
 // Cost class of a cell's items: one part of its source list against its first tile, iterations per lane x sinks
 // per lane; classes are half octaves, heaviest first.  The tiles of a cell's rest are lighter and share the
 // class on purpose: they wait on their loads more than they compute, and run best among heavier items (with a
 // class of their own, at the end of the list: uniform box of 2097152 particles 4.77 -> 5.07 ms).
-__device__ inline int cell_class(int n, int nsrc, int S, int max_lanes, int parts) {
-    const int L0 = tile_at(n, S, max_lanes, 0).L;
-    const int iters = (nsrc + L0 - 1) / L0;
+__device__ inline int cell_class(int iters, int S, int parts) {
     const float cost = (float)(iters / parts + 1) * (float)S + 16.0f;
     const int cls = kNumClasses - 1 - (int)(2.0f * log2f(cost));
     return cls < 0 ? 0 : (cls >= kNumClasses ? kNumClasses - 1 : cls);
@@ -196,8 +188,8 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
         if (n > 0) {
             const BoxDev B = boxes[b];
             nsrc = cell_sources<R>(cs, B, (int)(c - B.cell_base));
-            const int tiles = tile_count(n, S, max_lanes), L0 = tile_at(n, S, max_lanes, 0).L;
-            const unsigned long long iters = (unsigned long long)((nsrc + L0 - 1) / L0);
+            const int tiles = tile_count(n, S, max_lanes);
+            const unsigned long long iters = (unsigned long long)cell_iters(n, nsrc, S, max_lanes);
             w[0] += (unsigned long long)n * (unsigned long long)nsrc;
             w[1] += (unsigned long long)n * iters;
             w[2] += (unsigned long long)tiles * iters;
@@ -265,7 +257,7 @@ __global__ __launch_bounds__(256) void k_wl_cells(const int32_t *__restrict__ cs
 
 // Source iterations per lane of a wave's share of `pairs` pairs, at most part_sources.
 __device__ inline int fill_length(unsigned long long pairs, int S, int part_sources) {
-    const unsigned long long fill = pairs / ((unsigned long long)(64 * S) * kFillItems);
+    const unsigned long long fill = (pairs / (64 * kFillItems)) >> (S >> 1);   // S is 1, 2 or 4
     return fill > (unsigned long long)part_sources ? part_sources : (int)fill;
 }
 
@@ -293,7 +285,7 @@ __global__ __launch_bounds__(256) void k_wl_plan(WorkState *__restrict__ ws, Wor
         const long long want = fill_length(w.pairs, S, part_sources), least = least_part(w.pairs, S);
         const long long it = want < least ? least : want;
         // bounds at this length: slots <= n + slot_iters / length, items <= tiles + item_iters / length
-        const double slots = (double)(w.slot_iters / it + 1), items = (double)(w.item_iters / it + 1);
+        const double slots = (double)w.slot_iters / (double)it + 1.0, items = (double)w.item_iters / (double)it + 1.0;
         const double slot_room = (double)(box_slots(n) - n), item_room = (double)box_items(n, K * K * K) - (double)w.tiles;
         double f = 1.0;
         if (slots > slot_room) f = slot_room >= 1.0 ? slots / slot_room : 1e18;
@@ -312,12 +304,13 @@ __device__ inline int length_bin(int iters) {
     return b < 0 ? 0 : (b >= kNumClasses ? kNumClasses - 1 : b);
 }
 
-// Parts of a cell, negative where they stay together in one item per tile.
-__device__ inline int cell_split(int n, int nsrc, int S, int max_lanes, int part_iters, int whole_iters, int whole_bin) {
-    const int parts = cell_part_count(n, nsrc, S, max_lanes, part_iters);
-    if (parts <= 1) return parts;
-    const int L0 = tile_at(n, S, max_lanes, 0).L, iters = (nsrc + L0 - 1) / L0;
-    return iters <= whole_iters || length_bin(iters) <= whole_bin ? -parts : parts;
+// Parts of the source list of a cell that is not empty: as many as keep its first tile at about part_iters source
+// iterations per lane; negative where they stay together in one item per tile.
+__device__ inline int cell_split(int iters, int nsrc, int part_iters, int whole_iters, int whole_bin) {
+    int parts = (int)(((unsigned)iters + (unsigned)part_iters - 1u) / (unsigned)part_iters);
+    if (parts > nsrc) parts = nsrc;
+    if (parts <= 1) return 1;
+    return iters <= whole_iters || (whole_bin >= 0 && length_bin(iters) <= whole_bin) ? -parts : parts;
 }
 
 // Where the boxes' rooms add up to more than the lists hold: what splitting the cells of every length bin takes.
@@ -333,12 +326,13 @@ __global__ __launch_bounds__(256) void k_wl_bins(const int32_t *__restrict__ cs,
     const int n = c < n_cells ? cs[c + 1] - cs[c] : 0;
     if (n > 0) {
         const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
-        const int nsrc = cell_nsrc[c], parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, whole_iters, -1);
+        const int nsrc = cell_nsrc[c], iters = cell_iters(n, nsrc, S, max_lanes);
+        const int parts = cell_split(iters, nsrc, wb[b].part_iters, whole_iters, -1);
         const unsigned long long tiles = (unsigned long long)tile_count(n, S, max_lanes);
         atomicAdd(&items[kNumClasses], tiles);
         if (parts < 0 || parts > 1) atomicAdd(&slots[kNumClasses], (unsigned long long)n);
         if (parts > 1) {
-            const int L0 = tile_at(n, S, max_lanes, 0).L, bin = length_bin((nsrc + L0 - 1) / L0);
+            const int bin = length_bin(iters);
             atomicAdd(&slots[bin], (unsigned long long)n * (unsigned long long)(parts - 1));
             atomicAdd(&items[bin], tiles * (unsigned long long)(parts - 1));
         }
@@ -383,15 +377,16 @@ __global__ __launch_bounds__(256) void k_wl_count(const int32_t *__restrict__ cs
     unsigned long long local = 0;
     int parts = 0;
     if (c < n_cells) {
-        const int n = cs[c + 1] - cs[c];
-        const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
-        const int nsrc = cell_nsrc[c];
-        parts = cell_split(n, nsrc, S, max_lanes, wb[b].part_iters, whole_iters, ws->whole_bin);
+        const int n = cs[c + 1] - cs[c], nsrc = cell_nsrc[c];
+        if (n > 0) {
+            const int b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
+            const int iters = cell_iters(n, nsrc, S, max_lanes);
+            parts = cell_split(iters, nsrc, wb[b].part_iters, whole_iters, ws->whole_bin);
+            const int split = parts < 0 ? 1 : parts;
+            if (parts != 1) local = atomicAdd(&need, (unsigned long long)split * (unsigned long long)n);
+            atomicAdd(&hist[cell_class(iters, S, split)], tile_count(n, S, max_lanes) * split);
+        }
         cell_parts[c] = parts;
-        const int split = parts < 0 ? 1 : parts;
-        if (parts < 0 || parts > 1) local = atomicAdd(&need, (unsigned long long)split * (unsigned long long)n);
-        if (n > 0)
-            atomicAdd(&hist[cell_class(n, nsrc, S, max_lanes, split)], tile_count(n, S, max_lanes) * split);
     }
     __syncthreads();
     if (threadIdx.x == 0) base = need ? atomicAdd(&ws->partial_slots, need) : 0;
@@ -455,7 +450,7 @@ __global__ __launch_bounds__(256) void k_wl_emit(const int32_t *__restrict__ cs,
             b = n_boxes > 1 ? box_of_cell(boxes, n_boxes, (int32_t)c) : 0;
             parts = cell_parts[c] < 0 ? 1 : cell_parts[c];
             tiles = tile_count(n, S, max_lanes);
-            cls = cell_class(n, cell_nsrc[c], S, max_lanes, parts);
+            cls = cell_class(cell_iters(n, cell_nsrc[c], S, max_lanes), S, parts);
             local = atomicAdd(&cnt[cls], tiles * parts);
         }
     }

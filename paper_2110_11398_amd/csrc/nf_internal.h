@@ -62,7 +62,7 @@ constexpr int kLightClaim = 4;
 constexpr unsigned long long kFillItems = 16384, kFewItems = 2700;
 constexpr long long kMinPart = 256;
 __host__ __device__ inline long long least_part(unsigned long long pairs, int S) {
-    const long long few = (long long)(pairs / ((unsigned long long)(64 * S) * kFewItems));
+    const long long few = (long long)((pairs / (64 * kFewItems)) >> (S >> 1));   // S is 1, 2 or 4
     return few < kMinPart ? kMinPart : (few > 2 * kMinPart ? 2 * kMinPart : few);
 }
 
