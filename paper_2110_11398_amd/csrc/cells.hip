@@ -21,8 +21,8 @@
 //
 // Bound by memory: coordinates move in order three times (44 bytes read and 44 written per particle with the keys),
 // against one random 12-byte gather, a cache line each, when only keys and indices were sorted.  Clustered box of
-// 16.7 million particles in random order 866 -> 600 us, late-time box of 33.5 million 2006 -> 1570, 6 million 358 ->
-// 205, 2 million 154 -> 95.
+// 16.7 million particles in random order 866 -> 610 us, late-time box of 33.5 million 1960 -> 1570, 6 million 358 ->
+// 200, 2 million 154 -> 91.
 //
 // Every step is deterministic: particles of a cell stay in input order.
 #include <algorithm>
